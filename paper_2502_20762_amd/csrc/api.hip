@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -374,7 +375,7 @@ struct Layout {
   // state and intermediates (offsets from the workspace base)
   size_t feat[2], yhat[2], ed, zA, zB, y, partials, zpad, spare_bits;
   size_t dwa = 0, hid = 0;  // wide blocks (C > 256): depthwise output, hidden layer
-  // chains of C = 256 blocks in one launch: one progress word per tile
+  // chains of blocks in one launch (C <= 256): one progress word per tile
   // (zero at creation; every launch adds the same count to all) and a
   // timeout flag
   size_t chain_flags = 0, chain_status = 0;
@@ -712,8 +713,8 @@ bool build_layout(const ncodec_config& cfg, const float* w, Image& img, Layout& 
     L.hid = alloc(2 * fb);
   }
   L.y = alloc(lb);
-  if (C == 256) {
-    const size_t tiles = (size_t)((cfg.height / 8 + 7) / 8) * ((cfg.width / 8 + 15) / 16);
+  if (C <= 256) {
+    const size_t tiles = (size_t)((cfg.height / 8 + 7) / 8) * ((cfg.width / 8 + 7) / 8);
     L.chain_flags = alloc(tiles * 4);
     L.chain_status = alloc(4);
   }
@@ -778,8 +779,8 @@ struct ncodec_ctx {
   };
   bool use_graphs = false;
   GraphSlot graphs[2][2];  // [decode][cur]
-  // consecutive C = 256 blocks as one chain launch (when every tile fits
-  // the device at once; chain_fit: -1 not yet checked, 0 no, 1 yes)
+  // consecutive blocks as one chain launch (when every tile fits the device
+  // at once; chain_fit: -1 not yet checked, 0 no, 1 yes)
   bool chains = true;
   int chain_fit = -1;
   // Parallel coding (Fig. 6; supplementary "Parallel Coding"): the coded
@@ -789,6 +790,7 @@ struct ncodec_ctx {
   bool overlap = false;
   hipStream_t aux = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+  hipEvent_t ev_gate = nullptr;  // orders this context's chains after other streams'
   hipStream_t cap_stream = nullptr;
   std::vector<CapturedNode>* capturing = nullptr;
   bool is_int() const { return cfg.path == NCODEC_PATH_INT16; }
@@ -872,6 +874,8 @@ hipError_t pw(ncodec_ctx* ctx, const char* kind, int loader, int epi, const PwAr
   });
 }
 
+bool dc_tile64(const ncodec_ctx* ctx);
+
 hipError_t dcblock(ncodec_ctx* ctx, BlockArgs ba) {
   const int C = ctx->cfg.channels;
   const bool gated = ctx->cfg.block == NCODEC_BLOCK_GATED;
@@ -879,7 +883,7 @@ hipError_t dcblock(ncodec_ctx* ctx, BlockArgs ba) {
   return timed(ctx, "dcblock", [&] {
     if (ctx->is_int())
       return C == 256 && !gated ? launch_dcblock128_i16(ba, ctx->stream) : launch_dcblock_i16(C, gated, ba, ctx->stream);
-    return launch_dcblock_f16(C, gated, ba, ctx->stream);
+    return dc_tile64(ctx) ? launch_dcblock64_f16(C, gated, ba, ctx->stream) : launch_dcblock128_f16(gated, ba, ctx->stream);
   });
 }
 
@@ -904,17 +908,115 @@ PwArgs conv_args(const ncodec_ctx* ctx, const ConvDev& c, int K, int N, int P) {
   return a;
 }
 
-// Whether runs of DC blocks go as chain launches: C = 256 (fp16 either form,
-// int the LeakyReLU form), enabled, and every tile of the grid resident on the
-// device at once (checked once per context).
+// Tiles of the fp16 DC blocks: 8 x 8 pixels, or 8 x 16 for C = 256 frames of more
+// than 256 tiles of 8 x 8.  Up to 256 tiles each has a CU of its own, and the
+// smaller tile's block takes 0.6 of the larger one's time: per gated block of a
+// chain 13.4 against 21.2 us at 720p (240 tiles of 8 x 8).  But every tile streams
+// the whole block's weights from L2, so with two 8 x 8 tiles per CU that stream is
+// the bound: 25 against 23 us per LeakyReLU block of a chain at 1080p (510 tiles).
+// Below C = 256 the weights are a quarter of that or less.
+bool dc_tile64(const ncodec_ctx* ctx) {
+  return ctx->cfg.channels < 256 || dc64_grid(ctx->cfg.height / 8, ctx->cfg.width / 8) <= 256;
+}
+
+// Tiles of the context's block kernels (workgroups of one launch).
+int dc_tiles(const ncodec_ctx* ctx) {
+  const int h8 = ctx->cfg.height / 8, w8 = ctx->cfg.width / 8;
+  return !ctx->is_int() && dc_tile64(ctx) ? dc64_grid(h8, w8) : dc_grid(h8, w8);
+}
+
+// Whether runs of DC blocks may go as chain launches: fp16 at C = 64 .. 256
+// (either form), int at C = 256 (the LeakyReLU form), enabled, and every tile
+// of the grid resident on the device at once (checked once per context).
 bool chains_usable(ncodec_ctx* ctx) {
+  const int C = ctx->cfg.channels;
   const bool gated = ctx->cfg.block == NCODEC_BLOCK_GATED;
-  if (!ctx->chains || ctx->cfg.channels != 256 || (ctx->is_int() && gated)) return false;
+  if (!ctx->chains || C > 256 || (ctx->is_int() && (gated || C != 256))) return false;
   if (ctx->chain_fit < 0) {
-    const int resident = ctx->is_int() ? dcchain128_i16_resident() : dcchain128_resident(gated);
-    ctx->chain_fit = resident >= dc_grid(ctx->cfg.height / 8, ctx->cfg.width / 8) ? 1 : 0;
+    const int resident = ctx->is_int()    ? dcchain128_i16_resident()
+                         : dc_tile64(ctx) ? dcchain64_resident(C, gated)
+                                          : dcchain128_resident(gated);
+    ctx->chain_fit = resident >= dc_tiles(ctx) ? 1 : 0;
   }
   return ctx->chain_fit == 1;
+}
+
+// Blocks of the next launch of a run with n blocks left: a chain of up to
+// kMaxChain, or one.  The shortest chain is two blocks at C = 256, four below
+// (ncodec_kernels_per_frame promises one launch per block for shorter runs of
+// the small models).
+int next_launch(ncodec_ctx* ctx, int n) {
+  const int m = std::min(n, kMaxChain);
+  return m >= (ctx->cfg.channels == 256 ? 2 : 4) && chains_usable(ctx) ? m : 1;
+}
+
+// Chains on one device.  A chain's workgroups wait for each other, so two
+// chains that each hold part of the device and need the rest would wait until
+// both give up.  Within a process that is ruled out here: a chain launch on a
+// stream is ordered after the chains in flight on other streams, unless all of
+// them are small (at most a quarter of the CUs, so that the four hardware
+// queues' worth of them fit together).  Entries are per stream, added by the
+// launching context and removed when it is destroyed.
+struct ChainGate {
+  struct Entry {
+    const ncodec_ctx* ctx;
+    hipStream_t stream;
+    bool small;
+  };
+  std::mutex m;
+  std::vector<Entry> active;
+};
+constexpr int kMaxDevices = 64;
+ChainGate g_gates[kMaxDevices];
+
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
+}
+
+// Called before a chain (or a graph that holds one) is launched on ctx->stream.
+hipError_t gate_chain(ncodec_ctx* ctx) {
+  if (ctx->device < 0 || ctx->device >= kMaxDevices) return hipSuccess;
+  ChainGate& g = g_gates[ctx->device];
+  const hipStream_t st = ctx->stream;
+  const bool small = dc_tiles(ctx) <= 64;
+  std::lock_guard<std::mutex> lock(g.m);
+  bool own = false;
+  for (size_t i = 0; i < g.active.size();) {
+    ChainGate::Entry& e = g.active[i];
+    if (e.stream == st) {
+      own = true;
+      e.small = e.small && small;
+      ++i;
+      continue;
+    }
+    // nothing can be ordered across the edge of a capture
+    if ((small && e.small) || capturing(st) || capturing(e.stream)) {
+      ++i;
+      continue;
+    }
+    if (!ctx->ev_gate) {
+      const hipError_t err = hipEventCreateWithFlags(&ctx->ev_gate, hipEventDisableTiming);
+      if (err != hipSuccess) return err;
+    }
+    hipError_t err = hipEventRecord(ctx->ev_gate, e.stream);
+    if (err == hipSuccess) err = hipStreamWaitEvent(st, ctx->ev_gate, 0);
+    if (err != hipSuccess) return err;
+    // a later launch that must wait for e waits for this one if this is not small
+    if (small) ++i;
+    else g.active.erase(g.active.begin() + i);
+  }
+  if (!own) g.active.push_back({ctx, st, small});
+  return hipSuccess;
+}
+
+void leave_gate(const ncodec_ctx* ctx) {
+  if (ctx->device < 0 || ctx->device >= kMaxDevices) return;
+  ChainGate& g = g_gates[ctx->device];
+  std::lock_guard<std::mutex> lock(g.m);
+  for (size_t i = 0; i < g.active.size();)
+    if (g.active[i].ctx == ctx) g.active.erase(g.active.begin() + i);
+    else ++i;
 }
 
 // One DC block of either form, src -> dst.
@@ -955,23 +1057,20 @@ hipError_t run_block(ncodec_ctx* ctx, const BlockDev& b, const void* src, void* 
 }
 
 // Blocks 0 .. n - 1 of `blocks`, block k from src[k] into dst[k] (src[k + 1]
-// = dst[k]).  At C = 256 (int path: LeakyReLU form) runs of up to kMaxChain blocks go
-// as one chain launch when every tile of the grid fits the device at once;
-// otherwise (and for a run of one) one launch per block.  The timing log
-// counts blocks either way.
+// = dst[k]), as chain launches where next_launch says so, otherwise one launch
+// per block.  The timing log counts blocks either way.
 // With down set (the encoder's blocks, fp16) and the run's last launch a
-// chain, that launch also runs the 2x2 stride-2 downsample on each tile's last
-// block output (into down_y; dst[n - 1] is then not written) and *down_done
-// is set; otherwise the caller runs the downsample.
+// chain at C = 256, that launch also runs the 2x2 stride-2 downsample on each
+// tile's last block output (into down_y; dst[n - 1] is then not written) and
+// *down_done is set; otherwise the caller runs the downsample.
 hipError_t run_blocks(ncodec_ctx* ctx, const std::vector<BlockDev>& blocks, const std::vector<const void*>& src,
                       const std::vector<void*>& dst, const ConvDev* down = nullptr, void* down_y = nullptr,
                       bool* down_done = nullptr) {
   const int n = (int)blocks.size();
   const int h8 = ctx->cfg.height / 8, w8 = ctx->cfg.width / 8;
   const bool gated = ctx->cfg.block == NCODEC_BLOCK_GATED;
-  const bool chain = n >= 2 && chains_usable(ctx);
   for (int k0 = 0; k0 < n;) {
-    const int m = chain ? std::min(n - k0, kMaxChain) : 1;
+    const int m = next_launch(ctx, n - k0);
     if (m == 1) {
       const hipError_t e = run_block(ctx, blocks[k0], src[k0], dst[k0]);
       if (e != hipSuccess) return e;
@@ -989,15 +1088,19 @@ hipError_t run_blocks(ncodec_ctx* ctx, const std::vector<BlockDev>& blocks, cons
     ca.nb = m;
     ca.flags = ctx->p<int>(ctx->L.chain_flags);
     ca.status = ctx->p<int>(ctx->L.chain_status);
-    const bool fuse = down && !ctx->is_int() && k0 + m == n;
+    const bool fuse = down && !ctx->is_int() && ctx->cfg.channels == 256 && k0 + m == n;
     if (fuse) {
       ca.down_w = ctx->p(down->w);
       ca.down_b = ctx->p(down->bias);
       ca.down_y = down_y;
       *down_done = true;
     }
-    const hipError_t e = timed(ctx, fuse ? "dcblock_down" : "dcblock", [&] {
-      return ctx->is_int() ? launch_dcchain128_i16(ca, ctx->stream) : launch_dcchain128_f16(gated, ca, ctx->stream);
+    hipError_t e = ctx->capturing ? hipSuccess : gate_chain(ctx);
+    if (e != hipSuccess) return e;
+    e = timed(ctx, fuse ? "dcblock_down" : "dcblock", [&] {
+      return ctx->is_int()    ? launch_dcchain128_i16(ca, ctx->stream)
+             : dc_tile64(ctx) ? launch_dcchain64_f16(ctx->cfg.channels, gated, ca, ctx->stream)
+                              : launch_dcchain128_f16(gated, ca, ctx->stream);
     }, m);
     if (e != hipSuccess) return e;
     k0 += m;
@@ -1487,6 +1590,7 @@ ncodec_status run_graph(ncodec_ctx* ctx, bool decode, const void* p0, const void
   } else {
     NC_HIP(ctx, retarget(ctx, gs, decode, ptr), "graph update");
   }
+  if (chains_usable(ctx)) NC_HIP(ctx, gate_chain(ctx), "graph launch");
   NC_HIP(ctx, hipGraphLaunch(gs.exec, ctx->stream), "graph launch");
   return NCODEC_OK;
 }
@@ -1867,16 +1971,28 @@ ncodec_status ncodec_set_state(ncodec_ctx* ctx, const void* d_feat, const void* 
   return NCODEC_OK;
 }
 
-// Launches of a run of n DC blocks (chains: up to kMaxChain blocks each).
+// Launches of a run of n DC blocks.
 int block_launches(ncodec_ctx* ctx, int n) {
-  if (n < 2 || !chains_usable(ctx)) return n;
-  return (n + kMaxChain - 1) / kMaxChain;
+  int launches = 0;
+  for (; n > 0; ++launches) n -= next_launch(ctx, n);
+  return launches;
 }
 
-// Whether the encoder's last block launch carries the downsample (fp16: its
-// last run of blocks is a chain of at least two).
+// Whether the encoder's last block launch carries the downsample (fp16, C =
+// 256: its last run of blocks is a chain).
 bool down_fused(ncodec_ctx* ctx, int n) {
-  return !ctx->is_int() && n >= 2 && chains_usable(ctx) && n - kMaxChain * ((n - 1) / kMaxChain) >= 2;
+  if (ctx->is_int() || ctx->cfg.channels != 256) return false;
+  int m = 0;
+  for (; n > 0; n -= m) m = next_launch(ctx, n);
+  return m > 1;
+}
+
+// Whether any run of the context's blocks goes as a chain (C = 256: whether a
+// run of two would).
+bool chains_in_use(ncodec_ctx* ctx) {
+  const ncodec_config& c = ctx->cfg;
+  const int longest = std::max(std::max(c.n_enc_blocks, c.n_dec_blocks), std::max(c.n_fe_blocks, c.n_rg_blocks));
+  return next_launch(ctx, c.channels == 256 ? 2 : longest) > 1;
 }
 
 int32_t ncodec_kernels_per_frame(const ncodec_ctx* cctx, int32_t decode) {
@@ -1930,7 +2046,7 @@ ncodec_status ncodec_block_chain_status(ncodec_ctx* ctx, int32_t* in_use, int32_
   ncodec_status st = enter(ctx);
   if (st) return st;
   if (!in_use || !timeouts) return fail(ctx, NCODEC_EINVAL, "in_use and timeouts must not be NULL");
-  *in_use = block_launches(ctx, 2) == 1 ? 1 : 0;
+  *in_use = chains_in_use(ctx) ? 1 : 0;
   *timeouts = 0;
   if (!ctx->L.chain_status) return NCODEC_OK;
   int32_t v = 0;
@@ -1998,6 +2114,7 @@ void ncodec_destroy(ncodec_ctx* ctx) {
   if (!ctx) return;
   (void)hipSetDevice(ctx->device);
   (void)hipStreamSynchronize(ctx->stream);
+  leave_gate(ctx);
   for (auto& t : ctx->log) {
     if (t.start) (void)hipEventDestroy(t.start);
     if (t.stop) (void)hipEventDestroy(t.stop);
@@ -2012,6 +2129,7 @@ void ncodec_destroy(ncodec_ctx* ctx) {
     (void)hipStreamSynchronize(ctx->aux);
     (void)hipStreamDestroy(ctx->aux);
   }
+  if (ctx->ev_gate) (void)hipEventDestroy(ctx->ev_gate);
   if (ctx->ev_fork) (void)hipEventDestroy(ctx->ev_fork);
   if (ctx->ev_join) (void)hipEventDestroy(ctx->ev_join);
   delete ctx;

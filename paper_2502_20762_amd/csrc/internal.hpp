@@ -117,7 +117,7 @@ struct BlockArgs {
   const void* sig8 = nullptr;  // int path, gated form: compact sigmoid table (896 bytes)
 };
 
-// A run of DC blocks in one launch (the C = 256 chain kernels):
+// A run of DC blocks in one launch (the chain kernels):
 // blk[b].src = blk[b - 1].dst; flags: one int per tile, zero at workspace
 // creation and left equal across tiles by every launch; status: set to 1 if a
 // wait for a neighbouring tile timed out.
@@ -127,7 +127,7 @@ struct DcChainArgs {
   int nb;
   int* flags;
   int* status;
-  // fp16 chain only: when down_w is set, the last block's output stays in LDS
+  // fp16 chains at C = 256 only: when down_w is set, the last block's output stays in LDS
   // and feeds the 2x2 stride-2 downsample of the tile instead (down_w: its
   // weight fragments, K = 4C, N = C; down_b: C fp32 biases; down_y: the 1/16
   // output, NHWC), the same arithmetic as the downsample launch
@@ -200,7 +200,6 @@ hipError_t launch_rans_decode(const uint8_t* in, uint64_t in_bytes, const uint8_
 
 hipError_t launch_pw_f16(int loader, int epi, const PwArgs& a, hipStream_t st);
 hipError_t launch_pw_i16(int loader, int epi, const PwArgs& a, hipStream_t st);
-hipError_t launch_dcblock_f16(int C, bool gated, const BlockArgs& a, hipStream_t st);
 hipError_t launch_dcblock128_f16(bool gated, const BlockArgs& a, hipStream_t st);  // C = 256
 hipError_t launch_dcchain128_f16(bool gated, const DcChainArgs& ca, hipStream_t st);  // C = 256, fp16
 int dcchain128_resident(bool gated);
@@ -208,6 +207,10 @@ int dcchain128_resident(bool gated);
 hipError_t launch_dcblock128_i16(const BlockArgs& a, hipStream_t st);
 hipError_t launch_dcchain128_i16(const DcChainArgs& ca, hipStream_t st);
 int dcchain128_i16_resident();
+// fp16, C = 64, 128 or 256: 8 x 8 pixel tiles (one block, or a chain)
+hipError_t launch_dcblock64_f16(int C, bool gated, const BlockArgs& a, hipStream_t st);
+hipError_t launch_dcchain64_f16(int C, bool gated, const DcChainArgs& ca, hipStream_t st);
+int dcchain64_resident(int C, bool gated);
 hipError_t launch_dcblock_i16(int C, bool gated, const BlockArgs& a, hipStream_t st);
 hipError_t launch_prior_f16(const PriorArgs& a, hipStream_t st, int* n_partials);
 hipError_t launch_prior_i16(const PriorArgs& a, hipStream_t st, int* n_partials);
@@ -244,6 +247,12 @@ hipError_t launch_planar_to_nhwc(const void* src, void* dst, int C, int P, hipSt
 // DC-block kernels tile the 1/8-scale grid in 8 x 16 pixel tiles.
 inline int dc_grid(int h, int w) {
   const int t = ((h + 7) / 8) * ((w + 15) / 16);
+  return (t + 7) / 8 * 8;
+}
+
+// ... and the kernels of 8 x 8 pixel tiles
+inline int dc64_grid(int h, int w) {
+  const int t = ((h + 7) / 8) * ((w + 7) / 8);
   return (t + 7) / 8 * 8;
 }
 

@@ -4,10 +4,8 @@
 //               contractions (out^T = W * act^T + b) with gather-on-load and
 //               scatter-on-store, and the prior head with the quantiser and
 //               the bit partial sums as its epilogue (Fig. 4 "Q", Supp. B.2).
-// k_dcblock_f16 one whole DC block (Supp. B.1): depthwise 3x3, pw C->2C +
-//               LeakyReLU chained into pw 2C->C through registers 32 hidden
-//               channels at a time, residual add; or the gated form (WSiLU
-//               and Chunk, pw C->C) with the same pipeline.
+// k_pw256_f16   the same contractions at C = 256 in 256-row passes.
+// The DC blocks are in kernels_f16_dc64.hip and kernels_f16_dc128.hip.
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -489,471 +487,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NT == 64 ? 
   }
 }
 
-// One DC block (Supp. B.1) for a tile of 128 pixels, 8 waves.
-//
-// Waves w and w+4 share 32 pixels (pixel group w & 3) and sit on the same
-// SIMD; wave w >> 2 == hf owns output channels [hf C/2, (hf+1) C/2) of the
-// second pointwise conv and produces the hidden chunks j with j % 2 == hf of
-// the first one.  A hidden chunk (32 channels after bias + LeakyReLU, fp16)
-// goes to LDS in MFMA operand order so both waves of the pair consume it.
-//
-// The weights of one block are streamed in NCH = 2C/32 chunks: chunk j holds
-// the KS = C/16 pw1 fragments of hidden channels 32 j .. +31, their bias in
-// one more fragment (32 fp32 values that start the chain), then the 2 MT
-// pw2 fragments that consume them (one 1 KiB MFMA A fragment each), into a
-// ring of four LDS buffers with direct global->LDS loads (the loop is unrolled
-// by four, so every buffer address is static).  The residual is added from
-// LDS in the epilogue, so the prologue only exchanges the filtered channels.
-template <int C>
-struct DcSmem {
-  static constexpr int KS = C / 16, MT = C / 32, FR = KS + 1 + 2 * MT, CHUNK = FR * 1024;
-};
-
-// Fragments 0 .. n-1 of chunk j -> buf (n = FR, or KS + 1 for a gated h1
-// entry, whose pw2 slots are unused); fragment f is loaded by wave f % 8, so
-// every wave issues at least n / 8 loads.
-template <int C>
-__device__ __forceinline__ void dc_issue(const char* wchunks, int j, char* buf, int wave, int lane, int n) {
-  constexpr int FR = DcSmem<C>::FR;
-#pragma unroll
-  for (int i = 0; i < (FR + 7) / 8; ++i) {
-    const int f = wave + 8 * i;
-    if (f < n) dma16(wchunks + ((size_t)j * FR + f) * 1024 + lane * 16, buf + f * 1024);
-  }
-}
-
-// The first half of the pw1 fragments of one chunk, to registers.
-template <int C>
-__device__ __forceinline__ void dc_load_w1(const char* wb, int lane, half8* wf) {
-  const half8* w = (const half8*)wb + lane;
-#pragma unroll
-  for (int s = 0; s < DcSmem<C>::KS / 2; ++s) wf[s] = w[s * 64];
-}
-
-// pw1 chain of one hidden chunk, starting from its bias: the first half of
-// the fragments comes from registers (loaded an iteration earlier), the second
-// half and the bias are read from the chunk's buffer while the first half runs.
-template <int C>
-__device__ __forceinline__ floatx16 dc_hidden(const half8* wf, const char* wb, const half8* av, int lane) {
-  constexpr int KS = DcSmem<C>::KS;
-  const half8* w = (const half8*)wb + lane;
-  half8 w2[KS / 2];
-#pragma unroll
-  for (int s = 0; s < KS / 2; ++s) w2[s] = w[(KS / 2 + s) * 64];
-  // the bias: 32 fp32 values at the start of fragment KS; row 8 g + 4 h + e of
-  // the accumulator is element 4 g + e of lane half h
-  const int h = lane >> 5;
-  floatx4 bv[4];
-#pragma unroll
-  for (int g = 0; g < 4; ++g) bv[g] = *(const floatx4*)(wb + KS * 1024 + (8 * g + 4 * h) * 4);
-  __builtin_amdgcn_sched_barrier(0);
-  floatx16 hacc;
-#pragma unroll
-  for (int g = 0; g < 4; ++g)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) hacc[4 * g + e] = bv[g][e];
-#pragma unroll
-  for (int s = 0; s < KS / 2; ++s) hacc = mfma_f16(wf[s], av[s], hacc);
-#pragma unroll
-  for (int s = 0; s < KS / 2; ++s) hacc = mfma_f16(w2[s], av[KS / 2 + s], hacc);
-  return hacc;
-}
-
-// LeakyReLU, fp16; stored to `gx` as two B fragments (k = hidden in the
-// permuted order the pw2 weights were packed with).
-__device__ __forceinline__ void dc_hidden_store(const floatx16& hacc, int lane, half8* gx) {
-  half8 g0, g1;
-#pragma unroll
-  for (int g = 0; g < 4; ++g)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const f16 v = (f16)leaky(hacc[4 * g + e]);
-      if (g < 2) g0[4 * g + e] = v; else g1[4 * (g - 2) + e] = v;
-    }
-  gx[lane] = g0;
-  gx[64 + lane] = g1;
-}
-
-// Gated form.  WSiLU(h1) = h1 sigmoid(4 h1) of the h1 chain, kept as fp16 (8
-// registers) until the pair's h2 chain is done; then g = WSiLU(h1) * h2 for
-// the same elements, fp16, stored like dc_hidden_store.
-struct Wsilu16 {
-  half8 v[2];
-};
-__device__ __forceinline__ Wsilu16 dc_wsilu(const floatx16& h1) {
-  Wsilu16 w;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const float u = h1[r];
-    w.v[r >> 3][r & 7] = (f16)(u / (1.f + __expf(-4.f * u)));
-  }
-  return w;
-}
-__device__ __forceinline__ void dc_gate_store(const Wsilu16& s1, const floatx16& h2, int lane, half8* gx) {
-  half8 g0, g1;
-#pragma unroll
-  for (int g = 0; g < 4; ++g)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int r = 4 * g + e;
-      const f16 v = (f16)((float)s1.v[r >> 3][r & 7] * h2[r]);
-      if (g < 2) g0[4 * g + e] = v; else g1[4 * (g - 2) + e] = v;
-    }
-  gx[lane] = g0;
-  gx[64 + lane] = g1;
-}
-
-// Second pointwise conv, hidden chunk j, this wave's MT/2 output tiles.
-template <int C>
-__device__ __forceinline__ void dc_project(const char* wb, const half8* gx, int hf, int lane, floatx16* out) {
-  constexpr int KS = DcSmem<C>::KS, MT = DcSmem<C>::MT;
-  const half8* w = (const half8*)wb + lane;
-  const half8 g0 = gx[lane], g1 = gx[64 + lane];
-#pragma unroll
-  for (int t = 0; t < MT / 2; ++t) {
-    const int tt = hf * (MT / 2) + t;
-    out[t] = mfma_f16(w[(KS + 1 + 2 * tt) * 64], g0, out[t]);
-    out[t] = mfma_f16(w[(KS + 1 + 2 * tt + 1) * 64], g1, out[t]);
-  }
-}
-
-// Depthwise geometry of the DC block for C channels.  Wave w filters NCW
-// channels (block w % NCB) over NRW tile rows (block w / NCB); lane = channel
-// pair cp (fastest) x column slice colq of CPL columns, so each lane keeps its
-// 9 tap weights in registers and slides a 3 x 3 window over its columns.  The
-// wave's halo band ((NRW + 2) x 18 pixels x NCW channels) sits in its own LDS
-// region: halo pixel hp at position hp ^ ((hp >> 2) & 1), which puts the
-// pixels read by the column slices of one half-wave in different banks when
-// a pixel's slice is shorter than 128 bytes.  With C = 256 a wave takes 64
-// channels (whole 128-byte lines per halo pixel for its direct loads).
-template <int C>
-struct DcDw {
-  static constexpr int NCW = C == 256 ? 64 : C >= 128 ? C / 8 : 16;  // channels per wave
-  static constexpr int NRW = C / NCW;                 // tile rows per wave
-  static constexpr int NCB = C / NCW;                 // channel blocks
-  static constexpr int NCP = NCW / 2;                 // channel pairs
-  static constexpr int NCOLQ = 64 / NCP;              // column slices
-  static constexpr int CPL = 16 / NCOLQ;              // columns per lane
-  static constexpr int BP = (NRW + 2) * 18;           // halo pixels of the band
-  static constexpr int UPP = NCW / 8;                 // 16-byte units per halo pixel
-  static constexpr int SLOTS = BP * UPP;
-  static constexpr int RINSTR = (SLOTS + 63) / 64;    // direct loads per wave for the band
-  static constexpr int RB = SLOTS * 16;               // region bytes
-  static constexpr int XF = 1024 + 16;                // exchange fragment stride (padded against bank conflicts)
-  static constexpr int SPW = NCW / 16;                // 16-channel MFMA steps per wave
-  static_assert(NCB * (8 / NRW) == 8 && NCOLQ * CPL == 16 && BP % 2 == 0 && NRW % 2 == 0, "C in {64, 128, 256}");
-  static_assert(SPW * (NRW / 2) * XF <= RB, "the exchange fits the band's region");
-};
-
-__device__ __forceinline__ int dw_pos(int hp) { return hp ^ ((hp >> 2) & 1); }
-
-// GATED: the gated form (Supp. B.1, WSiLU and Chunk).  The weight entries
-// alternate: entry 2p holds the pw1 fragments and bias of h1 rows 32 p .. +31,
-// entry 2p + 1 those of the matching h2 rows and the pw2 fragments of gated
-// channels 32 p .. +31.  One wave produces both chains of pair p (wave p % 2
-// of its SIMD pair), keeps h1 in registers, and gates when h2 is done; the
-// pair is projected in the next iteration (odd entries), so even iterations
-// run no pw2.
-template <int C, bool GATED>
-__global__ __launch_bounds__(512) void k_dcblock_f16(BlockArgs a) {
-  using G = DcDw<C>;
-  constexpr int KS = DcSmem<C>::KS;
-  constexpr int NCH = 2 * C / 32;  // hidden chunks of 32 (a multiple of 4)
-  constexpr int MT = DcSmem<C>::MT;
-  constexpr int FR = DcSmem<C>::FR;
-  constexpr int TH = 8, TW = 16;   // pixel tile (rows x columns at 1/8 scale)
-  constexpr int CH8 = C / 8;       // 16-byte channel vectors per pixel
-  static_assert(NCH % 4 == 0, "chunk loop is unrolled by four");
-  // LDS: chunk buffers 0-3, the hidden-chunk buffers, the pw2 bias.  The
-  // eight band regions start after the pw1 part (fragments 0 .. KS) of buffer
-  // 1 and are laid over the rest, which is dead once the filtered channels have
-  // been exchanged.  So chunk 0 and the pw1 part of chunk 1 are loaded from
-  // the start, the pw2 part of chunk 1 after the exchange.  After the loop
-  // buffers 0-1 hold the residual tile and buffers 2-3 the parked output.
-  constexpr int BUF = DcSmem<C>::CHUNK;
-  constexpr int O1 = BUF, O2 = 2 * BUF, O3 = 3 * BUF, OGX = 4 * BUF;
-  constexpr int OR = BUF + (KS + 1) * 1024;  // first band region
-  constexpr int OB2 = (OR + 8 * G::RB > OGX + 16384 ? OR + 8 * G::RB : OGX + 16384);  // pw2 bias (C fp32)
-  constexpr int SMEM = OB2 + 1024;
-  static_assert(SMEM <= 160 * 1024, "fits the LDS of a CU");
-  static_assert(128 * C * 2 <= 2 * BUF && 2 * 32 * C * 2 <= BUF && BUF % 1024 == 0, "residual tile and parked output fit");
-  __shared__ __attribute__((aligned(1024))) char smem[SMEM];
-  char* const wb0 = smem;
-  char* const wb1 = smem + O1;
-  char* const wb2 = smem + O2;
-  char* const wb3 = smem + O3;
-  half8* const gx0 = (half8*)(smem + OGX);         // [pixel group][2 fragments x 64 lanes], even chunks
-  half8* const gx1 = (half8*)(smem + OGX + 8192);  // odd chunks
-
-  const int tiles_x = (a.w + TW - 1) / TW;
-  const int ntile = tiles_x * ((a.h + TH - 1) / TH);
-  const int tile = xcd_tile(blockIdx.x, gridDim.x);
-  if (tile >= ntile) return;
-  const int ty0 = (tile / tiles_x) * TH, tx0 = (tile % tiles_x) * TW;
-  const int lane = threadIdx.x & 63, h = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int pg = wave & 3, hf = wave >> 2;  // MFMA role: 32 pixels, half the outputs
-  const f16* z = (const f16*)a.src;
-  const char* wchunks = (const char*)a.w1;
-  auto region = [&](int w_) __attribute__((always_inline)) -> char* { return smem + OR + w_ * G::RB; };
-
-  // Depthwise role.
-  const int cbk = wave % G::NCB, rbk = wave / G::NCB;
-  const int cp = lane % G::NCP, colq = lane / G::NCP;
-  const int c0 = cbk * G::NCW + 2 * cp;  // this lane's channels c0, c0 + 1
-  char* const own = region(wave);
-  // this pair's 9 taps (fp16 pairs) and two fp32 biases: 48 bytes per pair
-  half2 wt[9];
-  float bias0, bias1;
-  {
-    // 11 words: a loaded word left unused would be reused as a temporary by
-    // the compiler, which then waits for this load before the band is issued
-    const intx4* wsrc = (const intx4*)a.dww + 3 * (c0 / 2);
-    const intx4 q0 = wsrc[0], q1 = wsrc[1];
-    const intx3 q2 = *(const intx3*)(wsrc + 2);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int x0 = q0[i], x1 = q1[i];
-      wt[i] = __builtin_bit_cast(half2, x0);
-      wt[4 + i] = __builtin_bit_cast(half2, x1);
-    }
-    const int x8 = q2[0], xb0 = q2[1], xb1 = q2[2];
-    wt[8] = __builtin_bit_cast(half2, x8);
-    bias0 = __builtin_bit_cast(float, xb0);
-    bias1 = __builtin_bit_cast(float, xb1);
-  }
-  // pw2 bias to LDS (wave 0, before its band: waited for with the band)
-  if (wave == 0 && lane < C / 4) dma16((const float*)a.b2 + 4 * lane, smem + OB2);
-  // Halo band: slot S = 16-byte unit S of the region holds unit S % UPP of
-  // halo pixel dw_pos(S / UPP); out-of-image pixels read the zero row.
-#pragma unroll
-  for (int i = 0; i < G::RINSTR; ++i) {
-    const int S = i * 64 + lane;
-    if (G::SLOTS % 64 == 0 || S < G::SLOTS) {
-      const int hp = dw_pos(S / G::UPP), u = S % G::UPP;
-      const int hy = ty0 + rbk * G::NRW - 1 + hp / 18, hx = tx0 - 1 + hp % 18;
-      const bool in = hy >= 0 && hy < a.h && hx >= 0 && hx < a.w;
-      dma16(in ? z + (size_t)(hy * a.w + hx) * C + cbk * G::NCW + 8 * u : (const f16*)a.zpad, own + i * 1024);
-    }
-  }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's band
-
-  // Chunk 0 and the pw1 part of chunk 1 (consumed after the depthwise) are
-  // requested a few fragments per output row, so that their direct loads,
-  // which the memory pipeline takes one at a time, queue behind the band
-  // instead of ahead of it.  Load m < NP0 is fragment wave + 8 m of chunk 0,
-  // the others fragment wave + 8 (m - NP0) of chunk 1.
-  constexpr int NP0 = (FR + 7) / 8, NP1 = (KS + 1 + 7) / 8;
-  constexpr int PER_ROW = (NP0 + NP1 + G::NRW - 1) / G::NRW;
-  auto issue_early = [&](int n) __attribute__((always_inline)) {
-#pragma unroll
-    for (int m = n * PER_ROW; m < (n + 1) * PER_ROW && m < NP0 + NP1; ++m) {
-      const int c1 = m >= NP0;
-      const int f = wave + 8 * (c1 ? m - NP0 : m);
-      if (f < (c1 ? KS + 1 : FR))
-        dma16(wchunks + ((size_t)c1 * FR + f) * 1024 + lane * 16, (c1 ? wb1 : wb0) + f * 1024);
-    }
-  };
-  // Depthwise 3x3 + bias: every band value this lane needs first, then the
-  // sliding window (fp32 accumulation), rounded to fp16.
-  half2 v[G::NRW + 2][G::CPL + 2];
-#pragma unroll
-  for (int y = 0; y < G::NRW + 2; ++y)
-#pragma unroll
-    for (int x = 0; x < G::CPL + 2; ++x)
-      v[y][x] = *(const half2*)(own + dw_pos(y * 18 + colq * G::CPL + x) * (G::UPP * 16) + cp * 4);
-  // The filtered pair goes straight to the MFMA B fragment of its pixel group
-  // and 16-channel step, in this wave's region (the band is dead once read):
-  // fragment (row pair j, step i) at (j SPW + i) XF; lane (pixel & 31) +
-  // 32 (bit 3 of the channel), element channel & 7.
-  const int xhalf = (cp >> 2) & 1;
-#pragma unroll
-  for (int rr = 0; rr < G::NRW; ++rr)
-#pragma unroll
-    for (int k = 0; k < G::CPL; ++k) {
-      float a0 = bias0, a1 = bias1;
-#pragma unroll
-      for (int ky = 0; ky < 3; ++ky)
-#pragma unroll
-        for (int kx = 0; kx < 3; ++kx) {
-          const half2 zz = v[rr + ky][k + kx], ww = wt[3 * ky + kx];
-          a0 = fmaf((float)ww[0], (float)zz[0], a0);
-          a1 = fmaf((float)ww[1], (float)zz[1], a1);
-        }
-      half2 o;
-      o[0] = (f16)a0;
-      o[1] = (f16)a1;
-      const int px = 16 * (rr & 1) + colq * G::CPL + k;  // pixel within the 32-pixel group
-      const int f = (rr >> 1) * G::SPW + (cp >> 3);
-      *(half2*)(own + f * G::XF + (px + 32 * xhalf) * 16 + (cp & 3) * 4) = o;
-      if (k == G::CPL - 1) issue_early(rr);
-    }
-  lds_barrier();
-
-  // MFMA role: all C filtered channels of this wave's 32 pixels.
-  half8 av[KS];
-#pragma unroll
-  for (int s = 0; s < KS; ++s) {
-    const int wcb = s / G::SPW, wrb = (2 * pg) / G::NRW;  // writer wave's channel and row blocks
-    const int f = (pg - wrb * (G::NRW / 2)) * G::SPW + (s - wcb * G::SPW);
-    av[s] = *(const half8*)(region(wrb * G::NCB + wcb) + f * G::XF + lane * 16);
-  }
-  lds_barrier();  // exchange read: the regions take buffers 2, 3 and the hidden chunks from here on
-
-  // Pipeline: in iteration j one wave of each pair runs the pw1 chain of
-  // hidden chunk j+1 from fragments it loaded in iteration j-1, the other loads
-  // the fragments of chunk j+2 for its next chain; both project hidden chunk
-  // j.  Chunk c sits in buffer c % 4; chunk j+3 is loaded during iteration j.
-  // Chunk 2 is only needed from iteration 1 on: it arrives during hidden
-  // chunk 0 and iteration 0, whose chain for chunk 2 loads its own fragments.
-  // the pw2 part of chunk 1 (2 MT fragments), then chunk 2
-#pragma unroll
-  for (int i = 0; i < (2 * MT + 7) / 8; ++i) {
-    const int f = KS + 1 + wave + 8 * i;
-    if ((2 * MT) % 8 == 0 || f < FR) dma16(wchunks + ((size_t)FR + f) * 1024 + lane * 16, wb1 + f * 1024);
-  }
-  dc_issue<C>(wchunks, 2, wb2, wave, lane, GATED ? KS + 1 : FR);  // gated: chunk 2 is an h1 entry
-  half8 wf[KS / 2];  // first half of the next chain's pw1 fragments
-  // chunk 0 and the pw1 part of chunk 1 (the rest of chunk 1 and chunk 2 in flight)
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * MT / 8 + (GATED ? KS + 1 : FR) / 8) : "memory");
-  lds_barrier();  // chunks 0 and 1 staged
-  Wsilu16 sw1 = {};  // gated: WSiLU of the h1 chain of the pair being produced
-  if (hf == 0) {
-    dc_load_w1<C>(wb0, lane, wf);
-    if constexpr (GATED) sw1 = dc_wsilu(dc_hidden<C>(wf, wb0, av, lane));
-    else dc_hidden_store(dc_hidden<C>(wf, wb0, av, lane), lane, gx0 + 128 * pg);
-  }
-  floatx16 out[MT / 2];  // pw2 accumulators, starting from the bias
-#pragma unroll
-  for (int t = 0; t < MT / 2; ++t) {
-    const int tt = hf * (MT / 2) + t;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const floatx4 bv = *(const floatx4*)(smem + OB2 + (32 * tt + 8 * g + 4 * h) * 4);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) out[t][4 * g + e] = bv[e];
-    }
-  }
-  if (hf == (GATED ? 0 : 1)) dc_load_w1<C>(wb1, lane, wf);  // chunk 1, for its chain in iteration 0
-  lds_barrier();  // hidden chunk 0 visible
-
-  // The residual tile (128 pixels x C fp16; 16-byte unit u of pixel px holds
-  // channel vector u ^ (px & 7); byte b of the tile in buffer 0 below BUF, in
-  // buffer 1 above) is loaded during the last two chunks.
-  auto rtile = [&](int b) __attribute__((always_inline)) -> char* { return b < BUF ? wb0 + b : wb1 + (b - BUF); };
-  auto issue_residual = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < C / 32; ++i) {
-      const int k = wave + 8 * i;  // 1 KiB unit k of the tile
-      const int S = k * 64 + lane;
-      const int px = S / CH8, k8 = (S % CH8) ^ (px & 7);
-      const int yy = ty0 + (px >> 4), xx = tx0 + (px & 15);
-      const bool in = yy < a.h && xx < a.w;
-      dma16(in ? z + (size_t)(yy * a.w + xx) * C + 8 * k8 : (const f16*)a.zpad, rtile(k * 1024));
-    }
-  };
-  auto step = [&](int j, const char* wcur, const char* wnxt, const char* wpre, char* wiss, half8* gcur, half8* gnxt)
-                  __attribute__((always_inline)) {
-    const bool dma = j + 3 < NCH;
-    if (dma) dc_issue<C>(wchunks, j + 3, wiss, wave, lane, GATED && !((j + 3) & 1) ? KS + 1 : FR);
-    // producer of chunk c: wave c % 2 of the pair, or in the gated form (c / 2) % 2
-    const int pj1 = GATED ? ((j + 1) >> 1) & 1 : (j + 1) & 1, pj2 = GATED ? ((j + 2) >> 1) & 1 : j & 1;
-    const bool produce = j + 1 < NCH && hf == pj1;
-    const bool prefetch = j >= 1 && j + 2 < NCH && hf == pj2;
-    floatx16 hacc;
-    if (produce) {
-      // the producer's chain is the iteration's critical path: its MFMAs go
-      // first on the SIMD, the partner's projection fills the gaps
-      __builtin_amdgcn_s_setprio(2);
-      if (j == 1) dc_load_w1<C>(wnxt, lane, wf);  // iteration 0 had no prefetch
-      hacc = dc_hidden<C>(wf, wnxt, av, lane);
-    }
-    if (j == NCH - 2) issue_residual();  // buffers 0 and 1 are free from here on
-    if (!GATED || (j & 1)) dc_project<C>(wcur, gcur, hf, lane, out);
-    if (prefetch) dc_load_w1<C>(wpre, lane, wf);
-    if (produce) {
-      if constexpr (GATED) {
-        if ((j + 1) & 1) dc_gate_store(sw1, hacc, lane, gnxt);  // h2 of the pair: gate it
-        else sw1 = dc_wsilu(hacc);
-      } else {
-        dc_hidden_store(hacc, lane, gnxt);
-      }
-    }
-    // chunk j+3 (in iteration 0 also chunk 2), or the residual in the last step
-    if (dma || j == NCH - 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_setprio(0);
-    lds_barrier();
-  };
-  for (int j = 0; j < NCH; j += 4) {
-    step(j + 0, wb0, wb1, wb2, wb3, gx0 + 128 * pg, gx1 + 128 * pg);
-    step(j + 1, wb1, wb2, wb3, wb0, gx1 + 128 * pg, gx0 + 128 * pg);
-    step(j + 2, wb2, wb3, wb0, wb1, gx0 + 128 * pg, gx1 + 128 * pg);
-    step(j + 3, wb3, wb0, wb1, wb2, gx1 + 128 * pg, gx0 + 128 * pg);
-  }
-
-  // Epilogue.  The residual enters the accumulators through the MFMA: for
-  // output tile tt, out += E0 z[32 tt .. +15] + E1 z[32 tt + 16 .. +31] with
-  // E0, E1 the two 32 x 16 halves of the identity (exact in fp32), the z
-  // fragments read from the residual tile in B layout.  Then the sums are
-  // rounded once to fp16 and parked in buffers 2 (pixel groups 0, 1) and 3
-  // (groups 2, 3), row = pixel, 8-byte unit u of the row at u ^ (row & 15);
-  // each thread finally stores 8 channels of one pixel with one 16-byte store.
-  {
-    const int row = lane & 31, px = 32 * pg + row;
-    half8 e0, e1;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      e0[e] = (f16)(row == 8 * h + e ? 1.f : 0.f);
-      e1[e] = (f16)(row == 16 + 8 * h + e ? 1.f : 0.f);
-    }
-#pragma unroll
-    for (int t = 0; t < MT / 2; ++t) {
-      const int tt = hf * (MT / 2) + t;
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const int k8 = 4 * tt + 2 * q + h;
-        const half8 zb = *(const half8*)rtile((px * CH8 + (k8 ^ (px & 7))) * 16);
-        out[t] = mfma_f16(q ? e1 : e0, zb, out[t]);
-      }
-    }
-    char* ob = (pg < 2 ? wb2 : wb3) + (pg & 1) * (32 * C * 2);
-#pragma unroll
-    for (int t = 0; t < MT / 2; ++t)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int cc = 32 * (hf * (MT / 2) + t) + 8 * g + 4 * h;
-        half4 o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = (f16)out[t][4 * g + e];
-        *(half4*)(ob + row * (C * 2) + (((cc >> 2) ^ (row & 15)) << 3)) = o;
-      }
-  }
-  lds_barrier();
-  constexpr int PER = 128 * CH8 / 512;  // 16-byte units per thread
-  f16* dst = (f16*)a.dst;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int idx = i * 512 + threadIdx.x;
-    const int px = idx / CH8, k8 = idx % CH8;
-    const int row = px & 31;
-    const int yy = ty0 + (px >> 4), xx = tx0 + (px & 15);
-    if (yy < a.h && xx < a.w) {
-      // units 2 k8 and 2 k8 + 1 are the aligned pair at 2 k8 ^ (row & 14),
-      // in swapped order when row is odd
-      const char* ob = (px < 64 ? wb2 : wb3) + ((px >> 5) & 1) * (32 * C * 2) + row * (C * 2);
-      const half8 pv = *(const half8*)(ob + (((2 * k8) ^ (row & 14)) << 3));
-      half8 o;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        o[e] = (row & 1) ? pv[4 + e] : pv[e];
-        o[4 + e] = (row & 1) ? pv[e] : pv[4 + e];
-      }
-      // streaming store: the block's output is read by the next launch, not this one
-      __builtin_nontemporal_store(o, (half8*)(dst + (size_t)(yy * a.w + xx) * C + 8 * k8));
-    }
-  }
-}
-
 // ------------------------------------------------- pointwise, 256-row passes
 // Contractions with 256-row passes and a plain or pixel-shuffled NHWC result
 // (the patch embed, K = 192 frame values, and the 2C -> C fuse, K = 512, one
@@ -1221,22 +754,6 @@ hipError_t launch_pw_f16(int loader, int epi, const PwArgs& a, hipStream_t st) {
   if ((epi == EP_LRELU || epi == EP_RESID || epi == EP_GATE) && a.N % 128 == 0)
     return pw_dispatch<128>(loader, epi, a, st);
   return pw_dispatch<64>(loader, epi, a, st);
-}
-
-hipError_t launch_dcblock_f16(int C, bool gated, const BlockArgs& a, hipStream_t st) {
-  // C = 256: the 128-pixels-per-wave kernel
-  if (C == 256) return launch_dcblock128_f16(gated, a, st);
-  dim3 grid(dc_grid(a.h, a.w)), block(512);
-  switch (C * 2 + (gated ? 1 : 0)) {
-    case 128: launch(k_dcblock_f16<64, false>, grid, block, st, a); break;
-    case 256: launch(k_dcblock_f16<128, false>, grid, block, st, a); break;
-    case 512: launch(k_dcblock_f16<256, false>, grid, block, st, a); break;
-    case 129: launch(k_dcblock_f16<64, true>, grid, block, st, a); break;
-    case 257: launch(k_dcblock_f16<128, true>, grid, block, st, a); break;
-    case 513: launch(k_dcblock_f16<256, true>, grid, block, st, a); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
 }
 
 // Channels per workgroup: 64 (mu and s rows, 128 accumulator registers), which
