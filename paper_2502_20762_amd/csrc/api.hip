@@ -608,8 +608,8 @@ bool build_layout(const ncodec_config& cfg, const float* w, Image& img, Layout& 
   if (is_int) {
     L.rec = pk.plain(rc_w, rc_b, 192, C);
   } else {
-    // 256 rows, 192 .. 255 zero: the 256-row pointwise kernel computes whole
-    // 64-row slices per wave and stores only the 192 frame rows
+    // 256 rows, 192 .. 255 zero: the pointwise kernel computes whole 64-row
+    // slices per wave and stores only the 192 frame rows
     std::vector<float> wpad((size_t)256 * C, 0.f), bpad(256, 0.f);
     std::copy(rc_w, rc_w + (size_t)192 * C, wpad.begin());
     std::copy(rc_b, rc_b + 192, bpad.begin());

@@ -199,6 +199,9 @@ hipError_t launch_rans_decode(const uint8_t* in, uint64_t in_bytes, const uint8_
                               uint32_t* errs, uint32_t* count, int16_t* q, int32_t* status_out, hipStream_t st);
 
 hipError_t launch_pw_f16(int loader, int epi, const PwArgs& a, hipStream_t st);
+// large register tiles: the pointwise halves of a wide DC block (EP_LRELU, EP_RESID, EP_GATE)
+// and the folded input convs of both transforms (LD_FRAME_CTX, LD_UP_CTX)
+hipError_t launch_pwt_f16(int loader, int epi, const PwArgs& a, hipStream_t st);
 hipError_t launch_pw_i16(int loader, int epi, const PwArgs& a, hipStream_t st);
 hipError_t launch_dcblock128_f16(bool gated, const BlockArgs& a, hipStream_t st);  // C = 256
 hipError_t launch_dcchain128_f16(bool gated, const DcChainArgs& ca, hipStream_t st);  // C = 256, fp16

@@ -4,8 +4,8 @@
 //               contractions (out^T = W * act^T + b) with gather-on-load and
 //               scatter-on-store, and the prior head with the quantiser and
 //               the bit partial sums as its epilogue (Fig. 4 "Q", Supp. B.2).
-// k_pw256_f16   the same contractions at C = 256 in 256-row passes.
-// The DC blocks are in kernels_f16_dc64.hip and kernels_f16_dc128.hip.
+// The larger contractions are in kernels_f16_pwt.hip, the DC blocks in
+// kernels_f16_dc64.hip and kernels_f16_dc128.hip.
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -50,8 +50,8 @@ __device__ __forceinline__ const char* pw_act_src(const PwArgs& a, int gp, int k
   if constexpr (LOADER == LD_NHWC) {
     if (k < a.C0) return (const char*)((const f16*)a.src0 + (size_t)gp * (a.ld0 ? a.ld0 : a.C0) + k);
     return (const char*)((const f16*)a.src1 + (size_t)gp * a.C1 + (k - a.C0));
-  } else if constexpr (LOADER == LD_FRAME || LOADER == LD_FRAME_CTX) {
-    if (LOADER == LD_FRAME_CTX && kc >= 3) return (const char*)((const f16*)a.src1 + (size_t)gp * a.C1 + (k - 192));
+  } else if constexpr (LOADER == LD_FRAME_CTX) {
+    if (kc >= 3) return (const char*)((const f16*)a.src1 + (size_t)gp * a.C1 + (k - 192));
     // unshuffle x8: k = 64 c + 8 i + j -> colour c = kc, frame row 8 py + i = 8 py + v, columns 8 px .. +7
     const int py = gp / a.w8, px = gp - py * a.w8;
     return (const char*)((const f16*)a.src0 + (size_t)kc * a.H * a.W + (size_t)(8 * py + v) * a.W + 8 * px);
@@ -403,48 +403,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NT == 64 ? 
       for (int w = 0; w < 8; ++w) t += redz[w];
       a.partials[tile] = t;
     }
-  } else if constexpr (EPI == EP_GATE) {
-    // rows 64 j .. 64 j + 31 of the pass are h1 of gated channels n0 / 2 + 32 j
-    // .. + 31, rows 64 j + 32 .. + 63 the matching h2 (the packed pw1 order).
-    // As the fused gated block: WSiLU(h1) = h1 sigmoid(4 h1) rounded to fp16,
-    // then g = WSiLU(h1) h2 rounded to fp16.
-    constexpr int G = NT / 64, GU = 128 * G * 4;  // units (pixel, group, 8 channels)
-#pragma unroll
-    for (int it = 0; it < GU / 512; ++it) {
-      const int idx = it * 512 + threadIdx.x;
-      const int px = idx / (4 * G), j = (idx >> 2) % G, g8 = idx & 3;
-      const int gp = tile * 128 + px;
-      if (gp < a.P) {
-        const floatx16 h1 = parked(px, 8 * j + g8), h2 = parked(px, 8 * j + 4 + g8);
-        half8 o;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float u = h1[e];
-          const f16 s1 = (f16)(u / (1.f + __expf(-4.f * u)));
-          o[e] = (f16)((float)s1 * h2[e]);
-        }
-        *(half8*)((f16*)a.dst + (size_t)gp * a.Cdst + n0 / 2 + 32 * j + 8 * g8) = o;
-      }
-    }
-  } else if constexpr (EPI == EP_REC) {
-    // rows of the pass: global rows n0 .. n0+NT = 64 c + 8 i + j; a 16-byte store
-    // covers the 8 frame pixels j of (colour c, row i) of one 1/8-scale pixel.
-    constexpr int UNITS = 128 * (NT / 8);
-#pragma unroll
-    for (int it = 0; it < UNITS / 512; ++it) {
-      const int idx = it * 512 + threadIdx.x;
-      const int nl8 = idx >> 7, px = idx & 127;  // consecutive threads walk pixels
-      const int gp = tile * 128 + px;
-      if (gp < a.P) {
-        const floatx16 r = parked(px, nl8);
-        const int n = n0 + 8 * nl8, c = n >> 6, i = (n >> 3) & 7;
-        const int py = gp / a.w8, pxx = gp - py * a.w8;
-        half8 o;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = (f16)fminf(fmaxf(r[e], 0.f), 1.f);
-        *(half8*)((f16*)a.dst + (size_t)c * a.H * a.W + (size_t)(8 * py + i) * a.W + 8 * pxx) = o;
-      }
-    }
   } else {
     constexpr int UNITS = 128 * (NT / 8);
 #pragma unroll
@@ -455,24 +413,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NT == 64 ? 
       if (gp < a.P) {
         const floatx16 r = parked(px, nl8);
         half8 o;
-        if constexpr (EPI == EP_LRELU) {
-          // as the fused block: the hidden value rounded to fp16, then
-          // max(h, 0.1 h) in fp16
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const f16 hv = (f16)r[e];
-            o[e] = __builtin_fmaxf16(hv, hv * (f16)0.1f);
-          }
-        } else if constexpr (EPI == EP_RESID) {
-          const half8 zr = *(const half8*)((const f16*)a.res + (size_t)gp * a.Cdst + n0 + 8 * nl8);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) o[e] = (f16)(r[e] + (float)zr[e]);
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) o[e] = (f16)r[e];
-        }
+        for (int e = 0; e < 8; ++e) o[e] = (f16)r[e];
         size_t off;
-        if constexpr (EPI == EP_NHWC || EPI == EP_LRELU || EPI == EP_RESID) {
+        if constexpr (EPI == EP_NHWC) {
           off = (size_t)gp * a.Cdst + n0 + 8 * nl8;
         } else {  // EP_UP: pass rows n = sp * C + c, all in one sub-position sp
           const int C = a.Cdst, n = n0 + 8 * nl8;
@@ -487,210 +431,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NT == 64 ? 
   }
 }
 
-// ------------------------------------------------- pointwise, 256-row passes
-// Contractions with 256-row passes and a plain or pixel-shuffled NHWC result
-// (the patch embed, K = 192 frame values, and the 2C -> C fuse, K = 512, one
-// pass each; the upsample, K = C, four passes = the four sub-positions of the
-// shuffle): out^T[256 rows of the pass][128 pixels] = W act^T + b for one tile
-// of 128 consecutive pixels per workgroup of 8 waves, the passes of a tile
-// next to each other on one XCD (they share the tile's activations in L2).  Waves 0 .. 3 (one per SIMD) compute: wave w owns rows
-// 64 w .. + 63 (two 32-row tiles) for all 128 pixels (four 32-pixel groups),
-// so each weight fragment it holds feeds four MFMAs; the fragments come
-// straight from global memory (L2) into registers as MFMA A operands, a few
-// k-steps ahead.  Waves 4 .. 7 load: the activation tile (K / 64 slices of 128
-// pixels x 64 contraction indices, 128-byte rows, 16-byte unit v of pixel p at
-// position v ^ ((p / 2) & 7)) arrives by their direct global->LDS loads, at
-// most DEPTH slices in flight, and each slice is released to the compute waves
-// by a barrier once it is in (with every CU requesting its whole tile at once,
-// the first slice would arrive only with the last).  Loads complete in order per wave,
-// so keeping the activation loads (HBM) and the weight loads (L2) in different
-// waves lets the weights stream while the activations are still arriving.  The
-// sums (bias first, fp32) are rounded to fp16 once, parked in LDS and stored as
-// 16-byte vectors (one contiguous block of 128 x 256 channels, or 512 bytes per
-// output pixel of the shuffle).
-template <int LOADER, int K, int EPI>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_pw256_f16(PwArgs a) {
-  constexpr int NK = K / 64;   // activation slices
-  constexpr int NS = K / 16;   // MFMA k-steps
-  constexpr int SLICE = 128 * 128;
-  constexpr int PA = 3, PB = 2;  // prefetch distances (steps) of the A and B windows
-  constexpr int DEPTH = 4;       // activation slices in flight
-  constexpr int SMEM = NK * SLICE > 128 * 512 ? NK * SLICE : 128 * 512;
-  static_assert(K % 64 == 0 && NK >= 2, "K is a multiple of 64, at least 128");
-  __shared__ __attribute__((aligned(1024))) char smem[SMEM];
-  static_assert(EPI == EP_NHWC || EPI == EP_UP || EPI == EP_REC, "plain or shuffled NHWC result, or the frame");
-  // EP_REC: N = 192 rows in one pass; the weight image and the bias are
-  // padded to 256 rows with zeros (wave 3's rows are computed and not stored)
-  const int ntile = (a.P + 127) / 128, npass = (a.N + 255) / 256;
-  const int lin = xcd_tile(blockIdx.x, gridDim.x);
-  const int tile = lin / npass;
-  if (tile >= ntile) return;
-  const int n0 = (lin - tile * npass) * 256;  // first row of the pass
-  // the upsample that follows the prior in an encode: workgroup 0 first adds
-  // up the frame's rate partials
-  if constexpr (EPI == EP_UP)
-    if (a.bits_out && blockIdx.x == 0) block_sum_to(a.sum_base, a.n_sum, a.bits_out);
-  const int lane = threadIdx.x & 63, h = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int myrow = lane & 31;
-
-  floatx16 acc[2][4];  // (row tile c, pixel group g)
-  if (wave >= 4) {
-    // ---- loaders: slice kc is 16 direct loads, instruction i = (wave - 4) + 4 m
-    const int lw = wave - 4;
-    auto load_slice = [&](int kc) __attribute__((always_inline)) {
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const int i = lw + 4 * m;
-        const int S = i * 64 + lane;
-        const int p = S >> 3, v = (S & 7) ^ ((p >> 1) & 7);
-        const int gp = min(tile * 128 + p, a.P - 1);  // pixels past the end reload the last one
-        dma16(pw_act_src<LOADER>(a, gp, kc, v, n0), smem + kc * SLICE + i * 1024);
-      }
-    };
-#pragma unroll
-    for (int kc = 0; kc < DEPTH && kc < NK; ++kc) load_slice(kc);
-    auto release = [&](auto kcc) __attribute__((always_inline)) {
-      constexpr int kc = decltype(kcc)::value;
-      constexpr int later = (kc + DEPTH < NK ? kc + DEPTH : NK) - 1 - kc;  // slices requested after kc
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * later) : "memory");  // slice kc is in
-      lds_barrier();
-      if constexpr (kc + DEPTH < NK) load_slice(kc + DEPTH);
-    };
-    unrolled_steps(release, std::make_integer_sequence<int, NK>{});
-  } else {
-    // ---- compute: rows 64 w + 32 c .., the accumulators start at the bias
-    const half8* wf = (const half8*)a.wfrag + lane;  // fragment (row tile mt, k-step s) at [(mt NS + s) 64]
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const float* b = (const float*)a.bias + n0 + 64 * wave + 32 * c + 4 * h;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const floatx4 bv = *(const floatx4*)(b + 8 * q);
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[c][g][4 * q + e] = bv[e];
-      }
-    }
-    auto afrag = [&](int s, int c) __attribute__((always_inline)) {
-      return wf[((size_t)(n0 / 32 + 2 * wave + c) * NS + s) * 64];
-    };
-    // B fragment of k-step s, group g: pixel 32 g + lane % 32, unit 2 (s % 4) + lane / 32 of slice s / 4
-    auto bfrag = [&](int s, int g) __attribute__((always_inline)) {
-      const int p = 32 * g + myrow, v = 2 * (s & 3) + h;
-      return *(const half8*)(smem + (s >> 2) * SLICE + p * 128 + ((v ^ ((p >> 1) & 7)) << 4));
-    };
-    half8 qa[PA][2], qb[PB][4];
-#pragma unroll
-    for (int s = 0; s < PA; ++s)
-#pragma unroll
-      for (int c = 0; c < 2; ++c) qa[s][c] = afrag(s, c);
-    lds_barrier();  // slice 0
-#pragma unroll
-    for (int s = 0; s < PB; ++s)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) qb[s][g] = bfrag(s, g);
-    // the barrier releasing slice kc + 1 is taken PB steps before slice kc
-    // ends, so the B window runs across the slices
-    auto step = [&](auto sc) __attribute__((always_inline)) {
-      constexpr int s = decltype(sc)::value;
-      if constexpr (s % 4 == 4 - PB && s / 4 + 1 < NK) lds_barrier();
-      half8 A[2], B[4];
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        A[c] = qa[s % PA][c];
-        if (s + PA < NS) qa[s % PA][c] = afrag(s + PA, c);
-      }
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        B[g] = qb[s % PB][g];
-        if (s + PB < NS) qb[s % PB][g] = bfrag(s + PB, g);
-      }
-#pragma unroll
-      for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) acc[c][g] = mfma_f16(A[c], B[g], acc[c][g]);
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    static_assert(PB <= 4, "the slice barrier precedes the B reads of the next slice");
-    unrolled_steps(step, std::make_integer_sequence<int, NS>{});
-  }
-  lds_barrier();  // every compute wave is done reading the slices
-  // park: one rounding to fp16, row = tile pixel (512 bytes), 8-byte unit u of
-  // the row at u ^ (row & 15)
-  if (wave < 4) {
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int p = 32 * g + myrow;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int cc = 64 * wave + 32 * c + 8 * q + 4 * h;
-          half4 o;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) o[e] = (f16)acc[c][g][4 * q + e];
-          *(half4*)(smem + p * 512 + (((cc >> 2) ^ (p & 15)) << 3)) = o;
-        }
-      }
-  }
-  lds_barrier();
-  if constexpr (EPI == EP_REC) {
-    // rows 64 c + 8 i + j: a 16-byte store covers the 8 frame pixels j of
-    // (colour c, row i) of one 1/8-scale pixel; consecutive threads walk the
-    // pixels, clamped to [0, 1] (the same as clamping before the rounding)
-#pragma unroll
-    for (int it = 0; it < 128 * 24 / 512; ++it) {
-      const int idx = it * 512 + threadIdx.x;
-      const int nl8 = idx >> 7, px = idx & 127;
-      const int gp = tile * 128 + px;
-      if (gp < a.P) {
-        const half8 pv = *(const half8*)(smem + px * 512 + (((2 * nl8) ^ (px & 14)) << 3));
-        const int c = nl8 >> 3, i = nl8 & 7;
-        const int py = gp / a.w8, pxx = gp - py * a.w8;
-        half8 o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const f16 v0 = (px & 1) ? pv[4 + e] : pv[e], v1 = (px & 1) ? pv[e] : pv[4 + e];
-          o[e] = __builtin_fminf16(__builtin_fmaxf16(v0, (f16)0.f), (f16)1.f);
-          o[4 + e] = __builtin_fminf16(__builtin_fmaxf16(v1, (f16)0.f), (f16)1.f);
-        }
-        __builtin_nontemporal_store(o, (half8*)((f16*)a.dst + (size_t)c * a.H * a.W + (size_t)(8 * py + i) * a.W + 8 * pxx));
-      }
-    }
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < 128 * 32 / 512; ++i) {
-    const int idx = i * 512 + threadIdx.x;
-    const int px = idx >> 5, k8 = idx & 31;  // tile pixel, 8-channel unit
-    const int gp = tile * 128 + px;
-    if (gp < a.P) {
-      const char* ob = smem + px * 512;
-      // units 2 k8 and 2 k8 + 1 are the aligned pair at 2 k8 ^ (px & 14), swapped when px is odd
-      const half8 pv = *(const half8*)(ob + (((2 * k8) ^ (px & 14)) << 3));
-      half8 o;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        o[e] = (px & 1) ? pv[4 + e] : pv[e];
-        o[4 + e] = (px & 1) ? pv[e] : pv[4 + e];
-      }
-      size_t off;
-      if constexpr (EPI == EP_NHWC) {
-        off = (size_t)gp * a.Cdst + n0 + 8 * k8;
-      } else {  // rows n = sp C + c: channel c of sub-position sp of the 2 x 2 shuffle
-        const int C = a.Cdst, n = n0 + 8 * k8;
-        const int sp = n / C, c = n - sp * C;
-        const int w16 = a.w8 >> 1;
-        const int Y = gp / w16, X = gp - Y * w16;
-        off = (size_t)((2 * Y + (sp >> 1)) * a.w8 + 2 * X + (sp & 1)) * C + c;
-      }
-      *(half8*)((f16*)a.dst + off) = o;
-    }
-  }
-}
-
 template <int NT>
 static hipError_t pw_dispatch(int loader, int epi, const PwArgs& a, hipStream_t st) {
   dim3 grid(grid_tiles(a.P) * (a.N / NT)), block(512);
@@ -699,24 +439,14 @@ static hipError_t pw_dispatch(int loader, int epi, const PwArgs& a, hipStream_t 
     launch(k_pw_f16<NT, L, E>, grid, block, st, a);                            \
     return hipGetLastError();                                                  \
   }
-  NC_PW(LD_NHWC, EP_NHWC)
-  NC_PW(LD_FRAME, EP_NHWC)
   NC_PW(LD_FRAME_CTX, EP_NHWC)
-  if constexpr (NT != 256) {
-    NC_PW(LD_DOWN, EP_NHWC)
-    NC_PW(LD_NHWC, EP_UP)
-    NC_PW(LD_UP_CTX, EP_UP)
-    NC_PW(LD_NHWC, EP_REC)
-    NC_PW(LD_NHWC, EP_LRELU)
-    NC_PW(LD_NHWC, EP_RESID)
-    NC_PW(LD_NHWC, EP_GATE)
-  }
-  if constexpr (NT == 64) {  // epilogues that pair two 32-row halves of a pass
-    NC_PW(LD_NHWC, EP_PRIOR)
-    NC_PW(LD_NHWC, EP_PRIOR_DEC)
-    NC_PW(LD_NHWC, EP_SCALES)
-    NC_PW(LD_DOWN, EP_ZQUANT)
-  }
+  NC_PW(LD_DOWN, EP_NHWC)
+  NC_PW(LD_NHWC, EP_UP)
+  NC_PW(LD_UP_CTX, EP_UP)
+  NC_PW(LD_NHWC, EP_PRIOR)
+  NC_PW(LD_NHWC, EP_PRIOR_DEC)
+  NC_PW(LD_NHWC, EP_SCALES)
+  NC_PW(LD_DOWN, EP_ZQUANT)
 #undef NC_PW
   return hipErrorInvalidValue;
 }
@@ -726,33 +456,11 @@ static hipError_t pw_dispatch(int loader, int epi, const PwArgs& a, hipStream_t 
 // 128, 256; 192 for the patch embed) and N a multiple of 64.
 hipError_t launch_pw_f16(int loader, int epi, const PwArgs& a, hipStream_t st) {
   if (a.K % 64 || a.N % 64) return hipErrorInvalidValue;
-  // The patch embed and the 2C -> C fuse have the widest activation tiles (K =
-  // 192 frame values or 2C channels) at 1/8 scale (one tile per CU or more):
-  // all N rows in one pass (N = 256: 48 KiB stages, one workgroup per CU) or
-  // 128 rows per pass, so each tile is staged once or twice.  The 1/16-scale
-  // kernels have 4x fewer tiles and keep 64-row passes to fill the CUs.
-  if ((epi == EP_NHWC && a.N == 256 && a.Cdst == 256 &&
-       ((loader == LD_FRAME && a.K == 192) || (loader == LD_NHWC && a.K == 512) ||
-        (loader == LD_FRAME_CTX && a.K == 448))) ||
-      (epi == EP_UP && a.N % 256 == 0 &&
-       ((loader == LD_NHWC && a.K == 256) || (loader == LD_UP_CTX && a.K == 512 && a.Cdst == 256))) ||
-      (epi == EP_REC && loader == LD_NHWC && a.K == 256 && a.N == 192 && a.C0 == 256 && a.ld0 == 0)) {
-    dim3 grid(grid_tiles(a.P) * ((a.N + 255) / 256)), block(512);
-    if (epi == EP_REC) launch(k_pw256_f16<LD_NHWC, 256, EP_REC>, grid, block, st, a);
-    else if (epi == EP_UP && loader == LD_UP_CTX) launch(k_pw256_f16<LD_UP_CTX, 512, EP_UP>, grid, block, st, a);
-    else if (epi == EP_UP) launch(k_pw256_f16<LD_NHWC, 256, EP_UP>, grid, block, st, a);
-    else if (loader == LD_FRAME) launch(k_pw256_f16<LD_FRAME, 192, EP_NHWC>, grid, block, st, a);
-    else if (loader == LD_FRAME_CTX) launch(k_pw256_f16<LD_FRAME_CTX, 448, EP_NHWC>, grid, block, st, a);
-    else launch(k_pw256_f16<LD_NHWC, 512, EP_NHWC>, grid, block, st, a);
-    return hipGetLastError();
-  }
-  if (epi == EP_NHWC && (loader == LD_FRAME || loader == LD_FRAME_CTX || (loader == LD_NHWC && a.K >= 512))) {
-    if (a.N == 256) return pw_dispatch<256>(loader, epi, a, st);
-    if (a.N % 128 == 0) return pw_dispatch<128>(loader, epi, a, st);
-  }
-  // the two halves of a wide DC block (C > 256) at 1/8 scale: 128-row passes
-  if ((epi == EP_LRELU || epi == EP_RESID || epi == EP_GATE) && a.N % 128 == 0)
-    return pw_dispatch<128>(loader, epi, a, st);
+  // the reconstruction, from C = 128 on the folded input convs and above C = 256 the
+  // two halves of a DC block: large register tiles
+  if (((loader == LD_FRAME_CTX || loader == LD_UP_CTX) && a.Cdst % 128 == 0) || epi == EP_REC || epi == EP_LRELU ||
+      epi == EP_RESID || epi == EP_GATE)
+    return launch_pwt_f16(loader, epi, a, st);
   return pw_dispatch<64>(loader, epi, a, st);
 }
 
