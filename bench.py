@@ -106,10 +106,10 @@ def cpu_baseline(pre, weights, strip_rows, path="fp16"):
 
 TRAFFIC_PROFILE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles", "dcblock_hd1080_hbm_traffic.md")
 CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2502_20762_amd", "csrc")
-SOURCES = {"k_dcchain128_f16<false>": ["kernels_f16_dc128.hip", "common.hpp", "internal.hpp"],
-           "k_dcblock128_f16<false>": ["kernels_f16_dc128.hip", "common.hpp", "internal.hpp"],
-           "k_dcchain128_i16": ["kernels_i16_dc128.hip", "common.hpp", "internal.hpp"],
-           "k_dcblock128_i16": ["kernels_i16_dc128.hip", "common.hpp", "internal.hpp"]}
+SOURCES = {"k_dcchain128_f16": ["kernels_f16_dc128.hip", "common.hpp", "internal.hpp"],
+           "k_dcblock128_f16": ["kernels_f16_dc128.hip", "common.hpp", "internal.hpp"],
+           "k_dcchain64_i16<256,false>": ["kernels_i16_dc64.hip", "common.hpp", "internal.hpp"],
+           "k_dcblock64_i16<256,false>": ["kernels_i16_dc64.hip", "common.hpp", "internal.hpp"]}
 
 
 def counted_traffic(kernel):
@@ -490,8 +490,8 @@ def main():
         # blocks either way
         chained = r["block_chains"]
         bpl = min(ne, nd, 16) if chained else 1
-        kname = ("k_dcchain128_f16<false>" if chained else "k_dcblock128_f16<false>") if path == "fp16" \
-            else ("k_dcchain128_i16" if chained else "k_dcblock128_i16")
+        kname = ("k_dcchain128_f16" if chained else "k_dcblock128_f16") if path == "fp16" \
+            else ("k_dcchain64_i16<256,false>" if chained else "k_dcblock64_i16<256,false>")
         traffic = counted_traffic(kname)
         K = args.steps
         fl, by = kinds["dcblock"]

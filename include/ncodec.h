@@ -358,29 +358,30 @@ int32_t ncodec_kernels_per_frame(const ncodec_ctx* ctx, int32_t decode);
 ncodec_status ncodec_graph_enable(ncodec_ctx* ctx, int32_t enable);
 
 /* Block chains (Sec. 3: fewer, larger modules per frame; Supp. B.1 blocks run
- * back to back).  On the fp16 path up to C = 256 (either block form) and on the
- * int16 path at C = 256 (the LeakyReLU form) the consecutive DC blocks of a
- * transform (the encoder's, the decoder's, the feature extractor's, the
- * reconstruction generation's; up to 16 per launch, from two blocks on at C =
- * 256, from four on below) run as one launch (fp16, C = 256: the encoder's
- * together with the downsample) in which every tile of the 1/8 grid (8 x 16
- * pixels; fp16 below C = 256 or up to 256 tiles: 8 x 8) keeps its block output
- * on chip and exchanges only its edge pixels with the neighbouring tiles
- * through memory.  Used only where every tile fits the device at once (checked
- * once per context with the occupancy API; at C = 256 one tile of 8 x 16 per
- * CU, 255 at 1080p); otherwise, and with enable = 0, one launch per block.
- * Results are identical either way.  On by default.  Chains of different
- * streams of a process are ordered one after the other unless they are small
- * (at most 64 tiles each).  A tile waits at most about 0.1 s for a neighbour (a
- * case that needs another kernel holding CUs for that long); a wait that gives
- * up leaves the block outputs wrong and is reported by
- * ncodec_block_chain_status.  Changing the setting drops captured graphs (the
- * next graph call captures again).  Errors: EINVAL for a NULL ctx, EHIP. */
+ * back to back).  Up to C = 256 the consecutive DC blocks of a transform (the
+ * encoder's, the decoder's, the feature extractor's, the reconstruction
+ * generation's; up to 16 per launch) run as one launch (fp16, C = 256: the
+ * encoder's together with the downsample) in which every tile of the 1/8 grid
+ * keeps its block output on chip and exchanges only its edge pixels with the
+ * neighbouring tiles through memory.  The shortest run that does is two blocks
+ * at C = 256, four for the small models and the integer gated form.  Tiles are 8 x
+ * 8 pixels, two per CU, or 8 x 16 for fp16 LeakyReLU blocks at C = 256 on
+ * frames of more than 320 tiles of 8 x 8.  Used only where every tile fits the
+ * device at once (checked once per context with the occupancy API; 510 tiles of
+ * 8 x 8 or 255 of 8 x 16 at 1080p), on the fp16 path below C = 256 up to 256
+ * tiles; otherwise, and with enable = 0, one launch per block.  Results are
+ * identical either way.  On by default.  Chains of different streams of a
+ * process are ordered one after the other unless they are small (at most 64
+ * tiles each).  A tile waits at most about 0.1 s for a neighbour (a case that
+ * needs another process's kernel holding CUs for that long); a wait that gives up
+ * leaves the block outputs wrong and is reported by ncodec_block_chain_status.
+ * Changing the setting drops captured graphs (the next graph call captures
+ * again).  Errors: EINVAL for a NULL ctx, EHIP. */
 ncodec_status ncodec_block_chains(ncodec_ctx* ctx, int32_t enable);
 
 /* *in_use = 1 if this context's DC blocks run as chains (enabled, a path, width
- * and form that have them, every tile resident at once and, below C = 256, a run of
- * four blocks or more), else 0.  Synchronizes the
+ * and size that have them, and where the shortest chain is four blocks, a run that
+ * long), else 0.  Synchronizes the
  * context's stream and writes to *timeouts 1 if any chain launch of this
  * context has given up waiting for a neighbouring tile since its creation,
  * else 0.  Errors: EINVAL for a NULL ctx, in_use or timeouts, EHIP. */

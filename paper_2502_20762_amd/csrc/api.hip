@@ -882,8 +882,8 @@ hipError_t dcblock(ncodec_ctx* ctx, BlockArgs ba) {
   if (gated && ctx->is_int()) ba.sig8 = ctx->p(ctx->L.sig8);
   return timed(ctx, "dcblock", [&] {
     if (ctx->is_int())
-      return C == 256 && !gated ? launch_dcblock128_i16(ba, ctx->stream) : launch_dcblock_i16(C, gated, ba, ctx->stream);
-    return dc_tile64(ctx) ? launch_dcblock64_f16(C, gated, ba, ctx->stream) : launch_dcblock128_f16(gated, ba, ctx->stream);
+      return launch_dcblock64_i16(C, gated, ba, ctx->stream);
+    return dc_tile64(ctx) ? launch_dcblock64_f16(C, gated, ba, ctx->stream) : launch_dcblock128_f16(ba, ctx->stream);
   });
 }
 
@@ -908,46 +908,57 @@ PwArgs conv_args(const ncodec_ctx* ctx, const ConvDev& c, int K, int N, int P) {
   return a;
 }
 
-// Tiles of the fp16 DC blocks: 8 x 8 pixels, or 8 x 16 for C = 256 frames of more
-// than 256 tiles of 8 x 8.  Up to 256 tiles each has a CU of its own, and the
-// smaller tile's block takes 0.6 of the larger one's time: per gated block of a
-// chain 13.4 against 21.2 us at 720p (240 tiles of 8 x 8).  But every tile streams
-// the whole block's weights from L2, so with two 8 x 8 tiles per CU that stream is
-// the bound: 25 against 23 us per LeakyReLU block of a chain at 1080p (510 tiles).
-// Below C = 256 the weights are a quarter of that or less.
+// Tiles of the DC blocks: 8 x 8 pixels, two per CU, or 8 x 16 pixels, one per CU, for
+// fp16 LeakyReLU blocks at C = 256 on frames of more than 320 tiles of 8 x 8 that still
+// run as a chain of 8 x 16 ones.  Up to 256 tiles of 8 x 8 each has a CU of its own; with
+// two per CU one's VALU and memory phases run beside the other's MFMA loops, but every
+// tile streams the whole block's weights from L2, which the larger tile halves.  us per
+// chained fp16 block at C = 256, 8 x 8 / 8 x 16: 720p gated (240 tiles) 13.4 / 21.2,
+// LeakyReLU 896 x 1280 (280) 18.1 / 19.3, 1024 x 1280 (320) 19.1 / 19.4, 1024 x 1536 (384)
+// 20.0 / 19.9, 1088 x 1664 (442) 21.9 / 20.9, 1080p (510) 22.2 / 21.9, 1080p gated 21.6 /
+// 22.7; one launch per block at 4K 84.8 / 91.7.  Integer blocks (twice the MFMAs per weight
+// byte, more VALU work): 1080p 33.7 / 38, 720p 22.5 / 36, 4K 129 / 153.
 bool dc_tile64(const ncodec_ctx* ctx) {
-  return ctx->cfg.channels < 256 || dc64_grid(ctx->cfg.height / 8, ctx->cfg.width / 8) <= 256;
+  const int h8 = ctx->cfg.height / 8, w8 = ctx->cfg.width / 8;
+  if (ctx->is_int() || ctx->cfg.channels < 256 || ctx->cfg.block == NCODEC_BLOCK_GATED) return true;
+  return dc64_grid(h8, w8) <= 320 || dc_grid(h8, w8) > 256;
 }
 
 // Tiles of the context's block kernels (workgroups of one launch).
 int dc_tiles(const ncodec_ctx* ctx) {
   const int h8 = ctx->cfg.height / 8, w8 = ctx->cfg.width / 8;
-  return !ctx->is_int() && dc_tile64(ctx) ? dc64_grid(h8, w8) : dc_grid(h8, w8);
+  return dc_tile64(ctx) ? dc64_grid(h8, w8) : dc_grid(h8, w8);
 }
 
-// Whether runs of DC blocks may go as chain launches: fp16 at C = 64 .. 256
-// (either form), int at C = 256 (the LeakyReLU form), enabled, and every tile
-// of the grid resident on the device at once (checked once per context).
+// Whether runs of DC blocks may go as chain launches: C = 64 .. 256, enabled, and
+// every tile of the grid resident on the device at once (checked once per context).
 bool chains_usable(ncodec_ctx* ctx) {
   const int C = ctx->cfg.channels;
   const bool gated = ctx->cfg.block == NCODEC_BLOCK_GATED;
-  if (!ctx->chains || C > 256 || (ctx->is_int() && (gated || C != 256))) return false;
+  if (!ctx->chains || C > 256) return false;
   if (ctx->chain_fit < 0) {
-    const int resident = ctx->is_int()    ? dcchain128_i16_resident()
+    const int resident = ctx->is_int()    ? dcchain64_i16_resident(C, gated)
                          : dc_tile64(ctx) ? dcchain64_resident(C, gated)
-                                          : dcchain128_resident(gated);
-    ctx->chain_fit = resident >= dc_tiles(ctx) ? 1 : 0;
+                                          : dcchain128_resident();
+    // fp16 below C = 256: with more than a tile per CU the exchange costs as much as
+    // the launches it saves (1080p, us per block chained / not: C = 128 10.2 / 10.1, C =
+    // 64 7.1 / 6.1; 832 x 480, C = 128 6.6 / 7.2)
+    const int most = !ctx->is_int() && C < 256 ? 256 : resident;
+    ctx->chain_fit = std::min(resident, most) >= dc_tiles(ctx) ? 1 : 0;
   }
   return ctx->chain_fit == 1;
 }
 
 // Blocks of the next launch of a run with n blocks left: a chain of up to
-// kMaxChain, or one.  The shortest chain is two blocks at C = 256, four below
-// (ncodec_kernels_per_frame promises one launch per block for shorter runs of
-// the small models).
+// kMaxChain, or one.  The shortest chain is two blocks at C = 256, but four for
+// the small models and the integer gated form (ncodec_kernels_per_frame and
+// ncodec_block_chain_status promise one launch per block for their shorter runs).
+int shortest_chain(const ncodec_ctx* ctx) {
+  return ctx->cfg.channels == 256 && !(ctx->is_int() && ctx->cfg.block == NCODEC_BLOCK_GATED) ? 2 : 4;
+}
 int next_launch(ncodec_ctx* ctx, int n) {
   const int m = std::min(n, kMaxChain);
-  return m >= (ctx->cfg.channels == 256 ? 2 : 4) && chains_usable(ctx) ? m : 1;
+  return m >= shortest_chain(ctx) && chains_usable(ctx) ? m : 1;
 }
 
 // Chains on one device.  A chain's workgroups wait for each other, so two
@@ -1084,6 +1095,7 @@ hipError_t run_blocks(ncodec_ctx* ctx, const std::vector<BlockDev>& blocks, cons
       ca.blk[j] = BlockArgs{ctx->p(b.pw1.w), nullptr, ctx->p(b.pw1.bias), ctx->is_int() ? nullptr : ctx->p(b.pw2.w),
                             nullptr, ctx->p(b.pw2.bias), ctx->p(b.dww), ctx->p(b.dwb), src[k0 + j], dst[k0 + j],
                             h8, w8, ctx->p(ctx->L.zpad)};
+      if (gated && ctx->is_int()) ca.blk[j].sig8 = ctx->p(ctx->L.sig8);
     }
     ca.nb = m;
     ca.flags = ctx->p<int>(ctx->L.chain_flags);
@@ -1098,9 +1110,11 @@ hipError_t run_blocks(ncodec_ctx* ctx, const std::vector<BlockDev>& blocks, cons
     hipError_t e = ctx->capturing ? hipSuccess : gate_chain(ctx);
     if (e != hipSuccess) return e;
     e = timed(ctx, fuse ? "dcblock_down" : "dcblock", [&] {
-      return ctx->is_int()    ? launch_dcchain128_i16(ca, ctx->stream)
-             : dc_tile64(ctx) ? launch_dcchain64_f16(ctx->cfg.channels, gated, ca, ctx->stream)
-                              : launch_dcchain128_f16(gated, ca, ctx->stream);
+      const int C = ctx->cfg.channels;
+      if (dc_tile64(ctx))
+        return ctx->is_int() ? launch_dcchain64_i16(C, gated, ca, ctx->stream)
+                             : launch_dcchain64_f16(C, gated, ca, ctx->stream);
+      return launch_dcchain128_f16(ca, ctx->stream);
     }, m);
     if (e != hipSuccess) return e;
     k0 += m;
@@ -1987,12 +2001,12 @@ bool down_fused(ncodec_ctx* ctx, int n) {
   return m > 1;
 }
 
-// Whether any run of the context's blocks goes as a chain (C = 256: whether a
-// run of two would).
+// Whether any run of the context's blocks goes as a chain (where two blocks chain:
+// whether a run of two would).
 bool chains_in_use(ncodec_ctx* ctx) {
   const ncodec_config& c = ctx->cfg;
   const int longest = std::max(std::max(c.n_enc_blocks, c.n_dec_blocks), std::max(c.n_fe_blocks, c.n_rg_blocks));
-  return next_launch(ctx, c.channels == 256 ? 2 : longest) > 1;
+  return next_launch(ctx, shortest_chain(ctx) == 2 ? 2 : longest) > 1;
 }
 
 int32_t ncodec_kernels_per_frame(const ncodec_ctx* cctx, int32_t decode) {

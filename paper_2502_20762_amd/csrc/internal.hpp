@@ -203,18 +203,17 @@ hipError_t launch_pw_f16(int loader, int epi, const PwArgs& a, hipStream_t st);
 // and the folded input convs of both transforms (LD_FRAME_CTX, LD_UP_CTX)
 hipError_t launch_pwt_f16(int loader, int epi, const PwArgs& a, hipStream_t st);
 hipError_t launch_pw_i16(int loader, int epi, const PwArgs& a, hipStream_t st);
-hipError_t launch_dcblock128_f16(bool gated, const BlockArgs& a, hipStream_t st);  // C = 256
-hipError_t launch_dcchain128_f16(bool gated, const DcChainArgs& ca, hipStream_t st);  // C = 256, fp16
-int dcchain128_resident(bool gated);
-// int path, LeakyReLU form, C = 256: 128 pixels per wave (one block, or a chain)
-hipError_t launch_dcblock128_i16(const BlockArgs& a, hipStream_t st);
-hipError_t launch_dcchain128_i16(const DcChainArgs& ca, hipStream_t st);
-int dcchain128_i16_resident();
+hipError_t launch_dcblock128_f16(const BlockArgs& a, hipStream_t st);  // C = 256, LeakyReLU: 8 x 16 pixel tiles
+hipError_t launch_dcchain128_f16(const DcChainArgs& ca, hipStream_t st);
+int dcchain128_resident();
 // fp16, C = 64, 128 or 256: 8 x 8 pixel tiles (one block, or a chain)
 hipError_t launch_dcblock64_f16(int C, bool gated, const BlockArgs& a, hipStream_t st);
 hipError_t launch_dcchain64_f16(int C, bool gated, const DcChainArgs& ca, hipStream_t st);
 int dcchain64_resident(int C, bool gated);
-hipError_t launch_dcblock_i16(int C, bool gated, const BlockArgs& a, hipStream_t st);
+// int path, the same tiles
+hipError_t launch_dcblock64_i16(int C, bool gated, const BlockArgs& a, hipStream_t st);
+hipError_t launch_dcchain64_i16(int C, bool gated, const DcChainArgs& ca, hipStream_t st);
+int dcchain64_i16_resident(int C, bool gated);
 hipError_t launch_prior_f16(const PriorArgs& a, hipStream_t st, int* n_partials);
 hipError_t launch_prior_i16(const PriorArgs& a, hipStream_t st, int* n_partials);
 int prior_partials_f16(int C, int P);

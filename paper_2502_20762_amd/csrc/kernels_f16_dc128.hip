@@ -1,5 +1,4 @@
-// fp16 DC block (Supp. B.1, LeakyReLU and gated forms) for C = 256 with 128 pixels per
-// wave: each wave covers the whole 8 x 16 pixel tile of its workgroup, so
+// fp16 DC block (Supp. B.1, LeakyReLU form) for C = 256 with 128 pixels per wave: each wave covers the whole 8 x 16 pixel tile of its workgroup, so
 // every weight fragment it loads feeds four MFMAs (the tile's four 32-pixel
 // groups).  The weight fragments are therefore read straight from global
 // memory (L2) into registers as MFMA A operands, never staged through LDS;
@@ -89,14 +88,6 @@ __device__ __forceinline__ void unrolled(F& f, std::integer_sequence<int, T...>)
   (f(std::integral_constant<int, T>{}), ...);
 }
 
-// GATED: the gated form (Supp. B.1, WSiLU and Chunk).  Its weight image pairs
-// the entries: entry 2 p holds the pw1 fragments of h1 rows 32 p .. +31,
-// entry 2 p + 1 those of the matching h2 rows and the pw2 fragments of gated
-// channels 32 p .. +31.  Round r's two chains of wave w are then h1 and h2 of
-// gated pair 4 r + w, and the hand-off writes g = WSiLU(h1) h2 (32 channels,
-// two k-steps) instead of the LeakyReLU of two chunks; pw2 contracts C = 256
-// gated channels (16 k-steps) instead of 2C.
-//
 // CHAIN: blocks 0 .. nb - 1 of a transform in one launch (blk[b] reads
 // blk[b - 1].dst).  Each tile keeps its block output in LDS, written straight
 // into the next block's band interior, so between blocks only the ring of the
@@ -200,13 +191,13 @@ __device__ __forceinline__ void dc128_down(const char* smem, const DcChainArgs& 
 // One block of a tile (FIRST: its band comes whole from a.src; LAST: its
 // output goes whole to a.dst, or with ca->down_w set through the fused
 // downsample to ca->down_y; otherwise the chain's ring and edge exchange).
-template <bool GATED, bool CHAIN, bool FIRST, bool LAST>
+template <bool CHAIN, bool FIRST, bool LAST>
 __device__ __forceinline__ void dc128_block(char* smem, const BlockArgs& a, int b, int tile, int tiles_x, int tiles_y,
                                             int wave0, int base, int* flags, int* status,
                                             const DcChainArgs* ca) {
   using namespace dcw;
-  constexpr int KH = GATED ? KS / 2 : KS;  // hidden k-steps per round (the pw2 k-steps of a round)
-  constexpr int NT = 2 * KS + 2 * KH;      // weight-stream steps: pw1 rounds 0, 1, pw2
+  constexpr int KH = KS;               // hidden k-steps per round (the pw2 k-steps of a round)
+  constexpr int NT = 2 * KS + 2 * KH;  // weight-stream steps: pw1 rounds 0, 1, pw2
   const int tyi = tile / tiles_x, txi = tile - tyi * tiles_x;
   const int ty0 = tyi * TH, tx0 = txi * TW;
   // the wave index, opaque to the compiler: keeps the weight-stream offsets
@@ -226,15 +217,14 @@ __device__ __forceinline__ void dc128_block(char* smem, const BlockArgs& a, int 
   const half8* wimg = (const half8*)a.w1 + lane;  // fragment (chunk j, f) at [(j FR + f) 64]
   // weight-stream step t, fragment c: pw1 round 0 (t < 16: entry 2 w + c,
   // k-step t), round 1 (t < 32: entry 8 + 2 w + c, k-step t - 16), pw2
-  // (k = t - 32: output tile 2 w + c, half k % 2 of the entry holding hidden
-  // chunk k / 2: entry k / 2, or 2 (k / 2) + 1 in the gated form)
+  // (k = t - 32: output tile 2 w + c, half k % 2 of hidden chunk k / 2's entry)
   auto afrag = [&](int t, int c) __attribute__((always_inline)) {
     int f;
     if (t < 2 * KS) {
       f = (8 * (t >> 4) + 2 * wave + c) * FR + (t & 15);
     } else {
       const int k = t - 2 * KS;
-      f = (GATED ? 2 * (k >> 1) + 1 : k >> 1) * FR + KS + 1 + 2 * (2 * wave + c) + (k & 1);
+      f = (k >> 1) * FR + KS + 1 + 2 * (2 * wave + c) + (k & 1);
     }
     return wimg[(size_t)f * 64];
   };
@@ -541,31 +531,9 @@ __device__ __forceinline__ void dc128_block(char* smem, const BlockArgs& a, int 
           *(half8*)(smem + off(g, 4 * wave + 2 * c + u) + myslot) = gv;
         }
   };
-  // Gated hand-off: WSiLU(h1) = h1 sigmoid(4 h1) rounded to fp16, then
-  // g = WSiLU(h1) h2 rounded to fp16 (h1, h2: the fp32 chains), as pw2 B
-  // fragments: half u of the pair goes to k-step 2 w + u of the round
-  auto gate_write = [&](auto off) __attribute__((always_inline)) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        half8 gv;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float h1 = acc[0][g][8 * u + e];
-          const f16 ws = (f16)(h1 / (1.f + __expf(-4.f * h1)));
-          gv[e] = (f16)((float)ws * acc[1][g][8 * u + e]);
-        }
-        *(half8*)(smem + off(g, 2 * wave + u) + myslot) = gv;
-      }
-  };
-  auto handoff = [&](auto off) __attribute__((always_inline)) {
-    if constexpr (GATED) gate_write(off);
-    else leaky_write(off);
-  };
   // pw1 chains of round r: the rows of entries 8 r + 2 w + c
   auto chain_row = [&](int r, int c) __attribute__((always_inline)) {
-    return GATED ? c * C + 32 * (4 * r + wave) : 32 * (8 * r + 2 * wave + c);
+    return 32 * (8 * r + 2 * wave + c);
   };
   // B fragment of step t, group g: a (pw1, k-step t % 16), then the hidden
   // layer (pw2, k-step t - 32: round 0 below 16, round 1 above)
@@ -592,7 +560,7 @@ __device__ __forceinline__ void dc128_block(char* smem, const BlockArgs& a, int 
     if constexpr (t == KS) {
       // round 0 done: its hidden fragments over the bands (no reader before
       // the hand-off barrier), then round 1 from its bias
-      handoff(h0_off);
+      leaky_write(h0_off);
       init_acc(chain_row(1, 0), chain_row(1, 1));
     }
     if constexpr (t == 2 * KS) {
@@ -600,7 +568,7 @@ __device__ __forceinline__ void dc128_block(char* smem, const BlockArgs& a, int 
       // read their operands at issue), its hidden fragments replace a; the
       // pw2 accumulators start from the bias
       lds_barrier();
-      handoff(a_off);
+      leaky_write(a_off);
       init_acc(2 * C + 64 * wave, 2 * C + 64 * wave + 32);
       // the residual enters first, through the identity (the two 32 x 16
       // halves as A, exact products); the sums are rounded to fp16 once
@@ -743,7 +711,7 @@ __device__ __forceinline__ void dc128_block(char* smem, const BlockArgs& a, int 
   }
 }
 
-template <bool GATED, bool CHAIN>
+template <bool CHAIN>
 __device__ __forceinline__ void dc128_body(const BlockArgs* blk, int nb, int* flags, int* status,
                                            const DcChainArgs* ca) {
   using namespace dcw;
@@ -753,50 +721,44 @@ __device__ __forceinline__ void dc128_body(const BlockArgs* blk, int nb, int* fl
   if (tile >= tiles_x * tiles_y) return;
   const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if constexpr (!CHAIN) {
-    dc128_block<GATED, false, true, true>(smem, blk[0], 0, tile, tiles_x, tiles_y, wave0, 0, nullptr, nullptr, nullptr);
+    dc128_block<false, true, true>(smem, blk[0], 0, tile, tiles_x, tiles_y, wave0, 0, nullptr, nullptr, nullptr);
   } else {
     // nb >= 2: the first block, the middle ones, the last
     const int base = __builtin_amdgcn_readfirstlane(__hip_atomic_load(flags + tile, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    dc128_block<GATED, true, true, false>(smem, blk[0], 0, tile, tiles_x, tiles_y, wave0, base, flags, status, ca);
+    dc128_block<true, true, false>(smem, blk[0], 0, tile, tiles_x, tiles_y, wave0, base, flags, status, ca);
     for (int b = 1; b < nb - 1; ++b)
-      dc128_block<GATED, true, false, false>(smem, blk[b], b, tile, tiles_x, tiles_y, wave0, base, flags, status, ca);
-    dc128_block<GATED, true, false, true>(smem, blk[nb - 1], nb - 1, tile, tiles_x, tiles_y, wave0, base, flags, status,
+      dc128_block<true, false, false>(smem, blk[b], b, tile, tiles_x, tiles_y, wave0, base, flags, status, ca);
+    dc128_block<true, false, true>(smem, blk[nb - 1], nb - 1, tile, tiles_x, tiles_y, wave0, base, flags, status,
                                           ca);
   }
 }
 
-template <bool GATED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_dcblock128_f16(BlockArgs a) {
-  dc128_body<GATED, false>(&a, 1, nullptr, nullptr, nullptr);
+  dc128_body<false>(&a, 1, nullptr, nullptr, nullptr);
 }
 
-template <bool GATED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_dcchain128_f16(DcChainArgs ca) {
-  dc128_body<GATED, true>(ca.blk, ca.nb, ca.flags, ca.status, &ca);
+  dc128_body<true>(ca.blk, ca.nb, ca.flags, ca.status, &ca);
 }
 
-hipError_t launch_dcblock128_f16(bool gated, const BlockArgs& a, hipStream_t st) {
-  if (gated) launch(k_dcblock128_f16<true>, dim3(dc_grid(a.h, a.w)), dim3(256), st, a);
-  else launch(k_dcblock128_f16<false>, dim3(dc_grid(a.h, a.w)), dim3(256), st, a);
+hipError_t launch_dcblock128_f16(const BlockArgs& a, hipStream_t st) {
+  launch(k_dcblock128_f16, dim3(dc_grid(a.h, a.w)), dim3(256), st, a);
   return hipGetLastError();
 }
 
-hipError_t launch_dcchain128_f16(bool gated, const DcChainArgs& ca, hipStream_t st) {
+hipError_t launch_dcchain128_f16(const DcChainArgs& ca, hipStream_t st) {
   if (ca.nb < 2 || ca.nb > kMaxChain) return hipErrorInvalidValue;
-  const dim3 grid(dc_grid(ca.blk[0].h, ca.blk[0].w));
-  if (gated) launch(k_dcchain128_f16<true>, grid, dim3(256), st, ca);
-  else launch(k_dcchain128_f16<false>, grid, dim3(256), st, ca);
+  launch(k_dcchain128_f16, dim3(dc_grid(ca.blk[0].h, ca.blk[0].w)), dim3(256), st, ca);
   return hipGetLastError();
 }
 
 // Workgroups of the chain kernel that fit the device at once (one per CU
 // with its 160 KiB of LDS); the chain needs every tile resident.
-int dcchain128_resident(bool gated) {
+int dcchain128_resident() {
   int dev = 0, per_cu = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  const hipError_t e = gated ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_dcchain128_f16<true>, 256, 0)
-                             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_dcchain128_f16<false>, 256, 0);
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_dcchain128_f16, 256, 0);
   return e == hipSuccess ? per_cu * cus : 0;
 }
 

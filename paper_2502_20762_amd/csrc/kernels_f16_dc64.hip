@@ -244,6 +244,11 @@ __device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b
     }
     return *(const half8*)(w1 + (size_t)f * 1024 + lane16);
   };
+  // of the two tiles on a CU, one leads in even blocks, the other in odd ones
+  if constexpr (!(FIRST && LAST)) {
+    if ((b ^ (blockIdx.x >> 8)) & 1) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+  }
   constexpr int PA = 4, PB = 2;  // prefetch distances (steps) of the A and B windows
   half8 qa[PA][2];
   auto nfrag = [](int t) constexpr { return t < N1 ? G::C1 : G::T2; };
@@ -692,7 +697,10 @@ __device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b
 // tiles, the next 256 the following ones, each range XCD by XCD, so that the
 // two tiles that share a CU lie far apart in the frame: in a chain they may
 // then run half a block out of step, one in its MFMA loops while the other is
-// in its VALU and memory phases.
+// in its VALU and memory phases.  (Left to themselves the first of the two, the older,
+// always goes first; the frame's second half then falls two blocks behind and
+// its neighbours wait: with the lead alternating from block to block a chained integer
+// block at 1080p takes 37.9 us instead of 39.3, gated 34.5 instead of 36.9.)
 __device__ __forceinline__ int dc64_tile() {
   const int slot = blockIdx.x >> 8, n = min(256, (int)gridDim.x - (slot << 8));
   return (slot << 8) + xcd_tile(blockIdx.x & 255, n);

@@ -1,16 +1,18 @@
-"""fp16 DC blocks on 8 x 8 pixel tiles: chains of blocks against one launch per block, which
+"""DC blocks on 8 x 8 pixel tiles, both paths: chains of blocks against one launch per block, which
 run the same per-block arithmetic (q, bits, state and decoded frame must agree bitwise, no
 wait may time out), for every width and form, at sizes with one tile, whole tiles, tiles cut at
-the right and bottom, and both sides of the 256-tile rule at C = 256.  The blocks
-themselves are checked against the oracle by the parity tests of every fp16 width.  Then
-chains of two contexts on two streams, enqueued from two threads at once."""
+the right and bottom, more tiles than CUs, and both sides of the rule between 8 x 8 and 8 x 16
+tiles (fp16, C = 256).  The blocks themselves are checked against the oracle by the parity
+tests of every width.  Then chains of two contexts on two streams, enqueued from two threads at once."""
 import threading
 
 import numpy as np
 import pytest
 import torch
 
+import oracle
 import synth
+from oracle import codec_int as ci
 from paper_2502_20762_amd.ncodec import Codec
 
 pytestmark = pytest.mark.gpu
@@ -23,9 +25,9 @@ def host(t):
     return t.cpu().numpy()
 
 
-def pair(H, W, C, ne, nd, block, **mods):
-    flat = synth.make_weights(C, ne, nd, block=block, n_fe=mods.get("n_fe_blocks", 0), n_rg=mods.get("n_rg_blocks", 0))
-    return [Codec(H, W, C, ne, nd, "fp16", flat, device=DEV, block=block, **mods) for _ in range(2)]
+def pair(H, W, C, ne, nd, block, path):
+    flat = synth.make_weights(C, ne, nd, block=block)
+    return [Codec(H, W, C, ne, nd, path, flat, device=DEV, block=block) for _ in range(2)]
 
 
 def run(enc, dec, frames, chains):
@@ -42,26 +44,62 @@ def run(enc, dec, frames, chains):
     return out
 
 
-@pytest.mark.parametrize("H,W,C,block,ne,nd", [
-    (64, 64, 64, "lrelu", 4, 4),      # one tile
-    (16, 16, 64, "gated", 4, 5),      # a part of one tile
-    (112, 208, 64, "gated", 4, 4),    # 14 x 26 pixels at 1/8: cut right and bottom
-    (480, 832, 128, "lrelu", 6, 6),
-    (112, 208, 128, "gated", 5, 4),
-    (272, 400, 256, "gated", 2, 3),
-    (1024, 1024, 256, "lrelu", 3, 2),  # 256 tiles of 8 x 8: the last size that takes them
-    (1024, 1040, 256, "lrelu", 3, 2),  # 272: 8 x 16 tiles
+@pytest.mark.parametrize("path,H,W,C,block,ne,nd", [
+    ("fp16", 64, 64, 64, "lrelu", 4, 4),      # one tile
+    ("int16", 64, 64, 64, "lrelu", 4, 4),
+    ("fp16", 16, 16, 64, "gated", 4, 5),      # a part of one tile
+    ("int16", 16, 16, 64, "gated", 4, 5),
+    ("fp16", 112, 208, 64, "gated", 4, 4),    # 14 x 26 pixels at 1/8: cut right and bottom
+    ("int16", 112, 208, 64, "gated", 4, 4),
+    ("fp16", 480, 832, 128, "lrelu", 6, 6),
+    ("int16", 480, 832, 128, "lrelu", 6, 6),
+    ("fp16", 112, 208, 128, "gated", 5, 4),
+    ("int16", 112, 208, 128, "gated", 5, 4),
+    ("fp16", 272, 400, 256, "gated", 2, 3),
+    ("int16", 272, 400, 256, "gated", 4, 5),
+    ("int16", 1024, 1280, 256, "gated", 4, 4),  # 320 tiles: two on some CUs
+    ("int16", 1024, 1280, 256, "lrelu", 3, 2),
+    ("fp16", 1024, 1280, 256, "lrelu", 3, 2),   # the last size that takes 8 x 8 tiles
+    ("fp16", 1024, 1296, 256, "lrelu", 3, 2),   # 336: 8 x 16 tiles
 ])
-def test_chains_match_one_launch_per_block(H, W, C, block, ne, nd):
-    enc, dec = pair(H, W, C, ne, nd, block)
+def test_chains_match_one_launch_per_block(path, H, W, C, block, ne, nd):
+    enc, dec = pair(H, W, C, ne, nd, block, path)
     frames = [synth.random_frame(H, W, seed=s) for s in (60, 61)]
-    print("[gpu-dc64]", H, W, C, block, flush=True)
+    print("[gpu-dc64]", path, H, W, C, block, flush=True)
     on = run(enc, dec, frames, True)
-    assert enc.kernels_per_frame(False) == (5 if C == 256 else 6)
+    # embed + fuse, chain, downsample (fp16, C = 256: in the chain), prior, up + fuse,
+    # chain; the int path runs embed, up and the two fuses apart
+    assert enc.kernels_per_frame(False) == (8 if path == "int16" else 5 if C == 256 else 6)
     off = run(enc, dec, frames, False)
     for t, (a, b) in enumerate(zip(on, off)):
         for what, u, v in zip(("q", "bits", "xhat", "f_t", "yhat"), a, b):
             np.testing.assert_array_equal(u, v, err_msg=f"frame {t}: {what}")
+
+
+@pytest.mark.parametrize("C,block,H,W", [(64, "gated", 80, 144), (128, "lrelu", 80, 144), (256, "gated", 80, 144),
+                                         (256, "lrelu", 144, 80)])
+def test_int_blocks_saturate_like_the_oracle(C, block, H, W):
+    # features and hidden values past the int16 range in every stage of the block: the
+    # context's columns of the fuse conv and the first block's pw1 are scaled up, so the
+    # rescales clip and the residual add saturates; Alg. 1's int32 contract holds (the
+    # oracle raises on an overflow)
+    flat = synth.make_weights(C, 1, 1, block=block).copy()
+    off, n = C * 192 + C, C * 2 * C
+    flat[off:off + n] *= 3
+    p = oracle.unpack(flat, C, 1, 1, block=block)
+    ip = ci.integerize(p)
+    rng = np.random.default_rng(C + H)
+    fprev = rng.integers(-12000, 12001, size=(C, H // 8, W // 8)).astype(np.int64)
+    st = ci.State(fprev, np.zeros((C, H // 16, W // 16), np.int64))
+    enc = Codec(H, W, C, 1, 1, "int16", flat, device=DEV, block=block)
+    enc.set_state(torch.from_numpy(fprev.astype(np.int16)).to(DEV),
+                  torch.zeros((C, H // 16, W // 16), dtype=torch.int16, device=DEV))
+    x = synth.random_frame(H, W, seed=62)
+    r = ci.encode_frame(ip, x, st)
+    assert np.abs(r.state.feat).max() >= 32767
+    q, _ = enc.encode(torch.from_numpy(x).to(DEV))
+    np.testing.assert_array_equal(host(q), r.q)
+    np.testing.assert_array_equal(host(enc.get_state()[0]).astype(np.int64), r.state.feat)
 
 
 def test_chains_on_two_streams():
