@@ -1665,7 +1665,7 @@ ncodec_status ncodec_create(const ncodec_config* cfg, const float* host_weights,
   ctx->L = std::move(L);
   hipError_t e = hipGetDevice(&ctx->device);
   if (e == hipSuccess) e = hipMemcpyAsync(ctx->ws, img.bytes.data(), img.bytes.size(), hipMemcpyHostToDevice, ctx->stream);
-  if (e == hipSuccess) e = launch_fill_zero(ctx->ws + ctx->L.image_bytes, ctx->L.total - ctx->L.image_bytes, ctx->stream);
+  if (e == hipSuccess) e = launch_fill_zero(ctx->ws + ctx->L.image_bytes, ctx->L.total - ctx->L.image_bytes, nullptr, 0, ctx->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
   if (e != hipSuccess) {
     g_create_error = std::string("create: ") + hipGetErrorString(e);
@@ -1705,8 +1705,9 @@ ncodec_status ncodec_reset(ncodec_ctx* ctx) {
   if (st) return st;
   const int C = ctx->cfg.channels;
   const size_t P8 = (size_t)(ctx->cfg.height / 8) * (ctx->cfg.width / 8);
-  NC_HIP(ctx, launch_fill_zero(ctx->p(ctx->L.feat[ctx->cur]), P8 * C * 2, ctx->stream), "reset");
-  NC_HIP(ctx, launch_fill_zero(ctx->p(ctx->L.yhat[ctx->cur]), P8 / 4 * C * 2, ctx->stream), "reset");
+  NC_HIP(ctx, launch_fill_zero(ctx->p(ctx->L.feat[ctx->cur]), P8 * C * 2, ctx->p(ctx->L.yhat[ctx->cur]), P8 / 4 * C * 2,
+                               ctx->stream),
+         "reset");
   return NCODEC_OK;
 }
 
@@ -1970,8 +1971,9 @@ ncodec_status ncodec_get_state(ncodec_ctx* ctx, void* d_feat, void* d_yhat) {
   if (st) return st;
   const int C = ctx->cfg.channels;
   const int P8 = (ctx->cfg.height / 8) * (ctx->cfg.width / 8);
-  if (d_feat) NC_HIP(ctx, launch_nhwc_to_planar(ctx->p(ctx->L.feat[ctx->cur]), d_feat, C, P8, ctx->stream), "get_state");
-  if (d_yhat) NC_HIP(ctx, launch_nhwc_to_planar(ctx->p(ctx->L.yhat[ctx->cur]), d_yhat, C, P8 / 4, ctx->stream), "get_state");
+  NC_HIP(ctx, launch_state_to_planar(ctx->p(ctx->L.feat[ctx->cur]), d_feat, P8, ctx->p(ctx->L.yhat[ctx->cur]), d_yhat,
+                                     P8 / 4, C, ctx->stream),
+         "get_state");
   return NCODEC_OK;
 }
 
@@ -1980,8 +1982,9 @@ ncodec_status ncodec_set_state(ncodec_ctx* ctx, const void* d_feat, const void* 
   if (st) return st;
   const int C = ctx->cfg.channels;
   const int P8 = (ctx->cfg.height / 8) * (ctx->cfg.width / 8);
-  if (d_feat) NC_HIP(ctx, launch_planar_to_nhwc(d_feat, ctx->p(ctx->L.feat[ctx->cur]), C, P8, ctx->stream), "set_state");
-  if (d_yhat) NC_HIP(ctx, launch_planar_to_nhwc(d_yhat, ctx->p(ctx->L.yhat[ctx->cur]), C, P8 / 4, ctx->stream), "set_state");
+  NC_HIP(ctx, launch_state_to_nhwc(d_feat, ctx->p(ctx->L.feat[ctx->cur]), P8, d_yhat, ctx->p(ctx->L.yhat[ctx->cur]),
+                                   P8 / 4, C, ctx->stream),
+         "set_state");
   return NCODEC_OK;
 }
 

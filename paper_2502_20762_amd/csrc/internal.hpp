@@ -225,7 +225,8 @@ constexpr int kBitsBlocks = 1024;
 // sigma = sigma_tab[s + 32768].  partials: kBitsBlocks doubles of scratch.
 hipError_t launch_estimate_bits(const int16_t* q, const void* scale, const float* sigma_tab, int64_t n,
                                 double* partials, double* out, hipStream_t st);
-hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);
+// zeroes two ranges (16-byte aligned, whole 16-byte units; bytes may be 0)
+hipError_t launch_fill_zero(void* p0, size_t bytes0, void* p1, size_t bytes1, hipStream_t st);
 // yhat (NHWC, C channels, P pixels) = q (planar int16) + mu (NHWC): fp16 path
 // (f16)(q + mu) with fp32 mu, int path clip(512 q + mu_i) with int16 mu_i --
 // the same operations as the quantiser of the prior epilogue.
@@ -243,8 +244,12 @@ hipError_t launch_zquant_i16(const PwArgs& a, hipStream_t st, int* n_partials);
 // int32 sum rescaled as every other convolution of the integer path.
 hipError_t launch_dw3x3_f16(const void* src, const void* dww, void* dst, int C, int h, int w, hipStream_t st);
 hipError_t launch_dw3x3_i16(const void* src, const void* dww, void* dst, int C, int h, int w, hipStream_t st);
-hipError_t launch_nhwc_to_planar(const void* src, void* dst, int C, int P, hipStream_t st);
-hipError_t launch_planar_to_nhwc(const void* src, void* dst, int C, int P, hipStream_t st);
+// both tensors of a state (f: Pf pixels, yhat: Py pixels) between the context's layout and
+// planar; a tensor whose source or destination is NULL is left out
+hipError_t launch_state_to_planar(const void* f_src, void* f_dst, int Pf, const void* y_src, void* y_dst, int Py, int C,
+                                  hipStream_t st);
+hipError_t launch_state_to_nhwc(const void* f_src, void* f_dst, int Pf, const void* y_src, void* y_dst, int Py, int C,
+                                hipStream_t st);
 
 // DC-block kernels tile the 1/8-scale grid in 8 x 16 pixel tiles.
 inline int dc_grid(int h, int w) {

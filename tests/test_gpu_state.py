@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import synth
-from paper_2502_20762_amd.ncodec import Codec
+from paper_2502_20762_amd.ncodec import Codec, ncodec_get_state, ncodec_set_state
 
 pytestmark = pytest.mark.gpu
 
@@ -35,3 +35,24 @@ def test_state_round_trip(H, W, C, path, shift):
     c.set_state(feat, yhat)
     for got, want in zip(c.get_state(), (feat, yhat)):
         assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
+def test_state_one_tensor_and_reset():
+    c = Codec(112, 208, 64, 1, 1, "int16", synth.make_weights(64, 1, 1), device=DEV)
+    g = torch.Generator(device=DEV).manual_seed(3)
+    f, y = (torch.randint(-30000, 30000, s, generator=g, device=DEV, dtype=torch.int32).to(torch.int16)
+            for s in (c.feat_shape, c.y_shape))
+    c.set_state(f, y)
+    # one tensor at a time (the other pointer NULL) leaves the other alone
+    f2 = f.flip(0).contiguous()
+    ncodec_set_state(c.ctx, f2.data_ptr(), 0)
+    got = torch.zeros_like(y)
+    ncodec_get_state(c.ctx, 0, got.data_ptr())
+    assert torch.equal(got, y) and torch.equal(c.get_state()[0], f2)
+    y2 = y.flip(0).contiguous()
+    ncodec_set_state(c.ctx, 0, y2.data_ptr())
+    assert torch.equal(c.get_state()[0], f2) and torch.equal(c.get_state()[1], y2)
+    ncodec_set_state(c.ctx, 0, 0)
+    assert torch.equal(c.get_state()[0], f2)
+    c.reset()
+    assert all(int(t.abs().max()) == 0 for t in c.get_state())
