@@ -729,7 +729,9 @@ bool build_layout(const ncodec_config& cfg, const float* w, Image& img, Layout& 
   L.spare_bits = alloc(8);        // bit total of graph replays called without d_bits
   L.n_z = cfg.hyperprior ? (int64_t)P32 * kCZ : 0;
   L.n_sym = (int64_t)P16 * C;
-  L.n_streams = (L.n_sym + kRansStream - 1) / kRansStream;
+  L.n_streams = rans_streams(L.n_sym);
+  if (cfg.hyperprior)  // the three containers of a frame are encoded at once
+    L.n_streams = std::max(L.n_streams, rans_streams(L.n_z) + 2 * rans_streams(L.n_sym / 2));
   L.kmap = alloc((size_t)L.n_sym);
   L.qtmp = alloc((size_t)(L.n_sym + L.n_z) * 2);
   L.rscratch = alloc((size_t)L.n_streams * kRansMaxWords * 2);
@@ -1789,9 +1791,10 @@ ncodec_status ncodec_rans_encode(ncodec_ctx* ctx, const int16_t* d_q, const uint
   if (capacity < stream_capacity(n))
     return fail(ctx, NCODEC_EINVAL, "capacity below the worst case of " + std::to_string(stream_capacity(n)) + " bytes");
   const Layout& L = ctx->L;
+  const RansSections secs{{{d_q, d_k, n, (uint8_t*)d_stream, d_stream_bytes, (int)rans_streams(n)}}, 1};
   NC_HIP(ctx, timed(ctx, "rans_enc", [&] {
-           return launch_rans_encode(d_q, d_k, n, rans_tab(ctx), ctx->p<uint16_t>(L.rscratch), kRansMaxWords,
-                                     ctx->p<uint32_t>(L.rlens), (uint8_t*)d_stream, d_stream_bytes, ctx->stream);
+           return launch_rans_encode(secs, rans_tab(ctx), ctx->p<uint16_t>(L.rscratch), kRansMaxWords,
+                                     ctx->p<uint32_t>(L.rlens), ctx->stream);
          }),
          "rans encode");
   return NCODEC_OK;
@@ -1827,28 +1830,28 @@ ncodec_status ncodec_encode_frame_coded(ncodec_ctx* ctx, const void* d_frame, in
   const bool par = ctx->overlap;
   if (par && (st = ensure_aux(ctx))) return st;
   int16_t* q = d_q ? d_q : ctx->p<int16_t>(L.qtmp);
-  // one container: all symbols; two-step model: z, y^1, y^2 at fixed offsets
-  auto section = [&](hipStream_t s, const int16_t* sq, const uint8_t* sk, int64_t n, size_t off,
-                     uint64_t* nbytes) -> ncodec_status {
-    NC_HIP(ctx, timed(ctx, "rans_enc", [&] {
-             return launch_rans_encode(sq, sk, n, rans_tab(ctx), ctx->p<uint16_t>(L.rscratch), kRansMaxWords,
-                                       ctx->p<uint32_t>(L.rlens), (uint8_t*)d_stream + off, nbytes, s);
-           }),
-           "rans encode");
-    return NCODEC_OK;
-  };
   // the coder: on the context's stream after the decoder, or (parallel coding)
   // on the second stream as soon as q and the scale indices exist, while the
   // decoder part of the encode runs (Fig. 6)
   auto coder = [&](hipStream_t s) -> ncodec_status {
+    // one container: all symbols; two-step model: z, y^1, y^2 at fixed offsets
     const uint8_t* k = ctx->p<uint8_t>(L.kmap);
-    if (!ctx->cfg.hyperprior) return section(s, q, k, L.n_sym, 0, d_stream_bytes);
-    const int64_t nh = L.n_sym / 2;
-    const size_t c0 = stream_capacity(L.n_z), c1 = stream_capacity(nh);
-    ncodec_status s2 = section(s, q + L.n_sym, ctx->p<uint8_t>(L.zk), L.n_z, 0, d_stream_bytes);
-    if (!s2) s2 = section(s, q, k, nh, c0, d_stream_bytes + 1);
-    if (!s2) s2 = section(s, q + nh, k + nh, nh, c0 + c1, d_stream_bytes + 2);
-    return s2;
+    uint8_t* const out = (uint8_t*)d_stream;
+    RansSections secs{{{q, k, L.n_sym, out, d_stream_bytes, (int)rans_streams(L.n_sym)}}, 1};
+    if (ctx->cfg.hyperprior) {
+      const int64_t nh = L.n_sym / 2;
+      const size_t c0 = stream_capacity(L.n_z), c1 = stream_capacity(nh);
+      secs.sec[0] = {q + L.n_sym, ctx->p<uint8_t>(L.zk), L.n_z, out, d_stream_bytes, (int)rans_streams(L.n_z)};
+      secs.sec[1] = {q, k, nh, out + c0, d_stream_bytes + 1, (int)rans_streams(nh)};
+      secs.sec[2] = {q + nh, k + nh, nh, out + c0 + c1, d_stream_bytes + 2, (int)rans_streams(nh)};
+      secs.count = 3;
+    }
+    NC_HIP(ctx, timed(ctx, "rans_enc", [&] {
+             return launch_rans_encode(secs, rans_tab(ctx), ctx->p<uint16_t>(L.rscratch), kRansMaxWords,
+                                       ctx->p<uint32_t>(L.rlens), s);
+           }, secs.count),
+           "rans encode");
+    return NCODEC_OK;
   };
   if (par) {
     st = enqueue_encode(ctx, d_frame, q, d_bits, ctx->p<uint8_t>(L.kmap), [&]() -> ncodec_status {

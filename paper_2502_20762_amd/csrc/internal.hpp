@@ -192,8 +192,25 @@ constexpr int kTabEncU16 = kTabBuckets;                       // what the encode
 constexpr int kTabU16 = kTabBuckets + kCoderScales * 257;     // what the decoder stages
 static_assert(kTabEncU16 % 8 == 0 && kTabU16 % 8 == 0, "coder table block must be whole 16-byte chunks");
 
-hipError_t launch_rans_encode(const int16_t* q, const uint8_t* k, int64_t n, const uint16_t* tab, uint16_t* scratch,
-                              int64_t max_words, uint32_t* lens, uint8_t* out, uint64_t* nbytes, hipStream_t st);
+inline int64_t rans_streams(int64_t n) { return (n + kRansStream - 1) / kRansStream; }
+// One container to be encoded: n symbols q with scale indices k into out, its size to
+// *nbytes; ns = rans_streams(n)
+struct RansSection {
+  const int16_t* q;
+  const uint8_t* k;
+  int64_t n;
+  uint8_t* out;
+  uint64_t* nbytes;
+  int ns;
+};
+constexpr int kRansMaxSections = 3;
+struct RansSections {
+  RansSection sec[kRansMaxSections];
+  int count;
+};
+// scratch (max_words per stream) and lens hold the streams of all sections
+hipError_t launch_rans_encode(const RansSections& secs, const uint16_t* tab, uint16_t* scratch, int64_t max_words,
+                              uint32_t* lens, hipStream_t st);
 // errs: one word per stream; count: a zero-initialised ticket counter, left at zero
 hipError_t launch_rans_decode(const uint8_t* in, uint64_t in_bytes, const uint8_t* k, int64_t n, const uint16_t* tab,
                               uint32_t* errs, uint32_t* count, int16_t* q, int32_t* status_out, hipStream_t st);
