@@ -203,8 +203,8 @@ __global__ __launch_bounds__(64) void k_rans_encode(RansSections secs, const uin
 // One workgroup per stream: the stream's place in its container is the sum of
 // the lengths before it (every workgroup sums them itself, so no separate scan
 // pass); a container's first workgroup also writes the header and the length table.
-__global__ __launch_bounds__(256) void k_rans_pack(RansSections secs, const uint16_t* scratch, int64_t max_words,
-                                                 const uint32_t* all_lens) {
+__global__ __launch_bounds__(256) void k_rans_pack(RansSections secs, const uint16_t* __restrict__ scratch,
+                                                 int64_t max_words, const uint32_t* __restrict__ all_lens) {
   __shared__ uint32_t sa[4], stot[4];
   int s = blockIdx.x;
   const RansSection& sec = section_of(secs, s);
@@ -230,7 +230,17 @@ __global__ __launch_bounds__(256) void k_rans_pack(RansSections secs, const uint
   const uint32_t len = lens[s];
   const uint16_t* src = scratch + (int64_t)(blockIdx.x + 1) * max_words - len;
   uint16_t* dst = (uint16_t*)(out + rans_payload_offset(ns)) + a;
-  for (uint32_t i = threadIdx.x; i < len; i += 256) dst[i] = src[i];
+  // eight loads in flight per thread (both ends lie at any word); one at a time took
+  // 8.6 us at 1080p (255 streams), this 6.0
+  uint32_t i = threadIdx.x;
+  for (; i + 7 * 256 < len; i += 8 * 256) {
+    uint16_t v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = src[i + 256 * e];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) dst[i + 256 * e] = v[e];
+  }
+  for (; i < len; i += 256) dst[i] = src[i];
   if (s == 0) {
     uint16_t* ltab = (uint16_t*)(out + kRansHeader);
     for (int i = threadIdx.x; i < ns; i += 256) ltab[i] = (uint16_t)lens[i];
