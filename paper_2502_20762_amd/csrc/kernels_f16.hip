@@ -8,6 +8,7 @@
 // kernels_f16_dc64.hip and kernels_f16_dc128.hip.
 #include "common.hpp"
 #include "internal.hpp"
+#include "pw_load.hpp"
 
 #include <cstring>
 #include <type_traits>
@@ -41,55 +42,16 @@ struct PwSmem {
   static constexpr int DMA_PER_WAVE = (ACT / 1024 + WGT / 1024) / 8;
 };
 
-// Global address of 16-byte activation vector v (8 contraction indices
-// starting at 64 kc + 8 v) of output pixel gp; n0 = the first output row of
-// the workgroup's pass.
-template <int LOADER>
-__device__ __forceinline__ const char* pw_act_src(const PwArgs& a, int gp, int kc, int v, int n0) {
-  const int k = 64 * kc + 8 * v;
-  if constexpr (LOADER == LD_NHWC) {
-    if (k < a.C0) return (const char*)((const f16*)a.src0 + (size_t)gp * (a.ld0 ? a.ld0 : a.C0) + k);
-    return (const char*)((const f16*)a.src1 + (size_t)gp * a.C1 + (k - a.C0));
-  } else if constexpr (LOADER == LD_FRAME_CTX) {
-    if (kc >= 3) return (const char*)((const f16*)a.src1 + (size_t)gp * a.C1 + (k - 192));
-    // unshuffle x8: k = 64 c + 8 i + j -> colour c = kc, frame row 8 py + i = 8 py + v, columns 8 px .. +7
-    const int py = gp / a.w8, px = gp - py * a.w8;
-    return (const char*)((const f16*)a.src0 + (size_t)kc * a.H * a.W + (size_t)(8 * py + v) * a.W + 8 * px);
-  } else if constexpr (LOADER == LD_UP_CTX) {
-    if (k < a.C0) return (const char*)((const f16*)a.src0 + (size_t)gp * a.C0 + k);
-    const int sp = n0 / a.Cdst, w16 = a.w8 >> 1;
-    const int Y = gp / w16, X = gp - Y * w16;
-    const int child = (2 * Y + (sp >> 1)) * a.w8 + 2 * X + (sp & 1);
-    return (const char*)((const f16*)a.src1 + (size_t)child * a.C1 + (k - a.C0));
-  } else {
-    // 2x2 stride 2: k = (2 i + j) Csrc + c from pixel (2 Y + i, 2 X + j)
-    const int w16 = a.w8 >> 1;
-    const int Y = gp / w16, X = gp - Y * w16;
-    const int tap = k / a.Csrc, c = k - tap * a.Csrc;
-    const int pix = (2 * Y + (tap >> 1)) * a.w8 + 2 * X + (tap & 1);
-    return (const char*)((const f16*)a.src0 + (size_t)pix * a.Csrc + c);
-  }
-}
-
 template <int NT, int LOADER>
-__device__ __forceinline__ void pw_issue(const PwArgs& a, int tile, int n0, int kc, char* stage, int wave, int lane) {
+__device__ __forceinline__ void pw_issue(const PwArgs& a, PwAct<LOADER>& act, int n0, int kc, char* stage, int wave, int lane) {
   using S = PwSmem<NT>;
-  constexpr int ACT_INSTR = S::ACT / 1024;  // 16
-#pragma unroll
-  for (int i = 0; i < ACT_INSTR / 8; ++i) {
-    const int ins = wave + 8 * i;
-    const int slot = ins * 64 + lane;
-    const int px = slot >> 3, v = (slot & 7) ^ ((px >> 1) & 7);
-    const int gp = min(tile * 128 + px, a.P - 1);  // pixels past the end reload the last one
-    dma16(pw_act_src<LOADER>(a, gp, kc, v, n0), stage + ins * 1024);
-  }
+  act.issue(a, kc, stage, wave);
   const int ks = a.K / 16;
-  const char* w = (const char*)a.wfrag;
 #pragma unroll
   for (int i = 0; i < S::WGT / 1024 / 8; ++i) {
     const int f = wave + 8 * i;  // fragment f of the stage: row tile f / 4, k-step f % 4
     const int mt = n0 / 32 + (f >> 2), sk = 4 * kc + (f & 3);
-    dma16(w + (((size_t)mt * ks + sk) * 64 + lane) * 16, stage + S::ACT + f * 1024);
+    dma16s((const char*)a.wfrag + ((size_t)mt * ks + sk) * 1024, lane * 16, stage + S::ACT + f * 1024);
   }
 }
 
@@ -146,8 +108,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NT == 64 ? 
 #pragma unroll
     for (int g = 0; g < 4; ++g) bias[t][g] = *(const floatx4*)((const float*)a.bias + n0 + 32 * (hf * RT + t) + 8 * g + 4 * h);
 
-  pw_issue<NT, LOADER>(a, tile, n0, 0, st0, wave, lane);
-  if (nk > 1) pw_issue<NT, LOADER>(a, tile, n0, 1, st1, wave, lane);
+  PwAct<LOADER> act;
+  act.init(a, tile, n0, wave, lane);
+  pw_issue<NT, LOADER>(a, act, n0, 0, st0, wave, lane);
+  if (nk > 1) pw_issue<NT, LOADER>(a, act, n0, 1, st1, wave, lane);
   // Stage kc: wait until at most the later-issued stages are in flight, make
   // every wave's loads visible, refill the buffer freed in the previous
   // iteration with stage kc + 3, then compute.
@@ -156,7 +120,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NT == 64 ? 
     if (ahead == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(S::DMA_PER_WAVE) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();
-    if (kc + 2 < nk) pw_issue<NT, LOADER>(a, tile, n0, kc + 2, refill, wave, lane);
+    if (kc + 2 < nk) pw_issue<NT, LOADER>(a, act, n0, kc + 2, refill, wave, lane);
     pw_compute<NT>(cur, pg, hf, lane, acc);
   };
   for (int kc = 0; kc < nk; kc += 3) {

@@ -13,6 +13,7 @@
 // a / 8192 and saturates to int16.
 #include "common.hpp"
 #include "internal.hpp"
+#include "pw_load.hpp"
 
 #include <cstring>
 
@@ -51,42 +52,16 @@ struct PwSmemIN {
   static constexpr int DMA_PER_WAVE = (PwSmemI::ACT / 1024 + WGT / 1024) / 8;
 };
 
-template <int LOADER>
-__device__ __forceinline__ const char* pwi_act_src(const PwArgs& a, int gp, int kc, int v) {
-  const int k = 64 * kc + 8 * v;
-  if constexpr (LOADER == LD_NHWC) {
-    if (k < a.C0) return (const char*)((const int16_t*)a.src0 + (size_t)gp * (a.ld0 ? a.ld0 : a.C0) + k);
-    return (const char*)((const int16_t*)a.src1 + (size_t)gp * a.C1 + (k - a.C0));
-  } else if constexpr (LOADER == LD_FRAME) {
-    const int py = gp / a.w8, px = gp - py * a.w8;
-    return (const char*)((const f16*)a.src0 + (size_t)kc * a.H * a.W + (size_t)(8 * py + v) * a.W + 8 * px);
-  } else {
-    const int w16 = a.w8 >> 1;
-    const int Y = gp / w16, X = gp - Y * w16;
-    const int tap = k / a.Csrc, c = k - tap * a.Csrc;
-    const int pix = (2 * Y + (tap >> 1)) * a.w8 + 2 * X + (tap & 1);
-    return (const char*)((const int16_t*)a.src0 + (size_t)pix * a.Csrc + c);
-  }
-}
-
 template <int NT, int LOADER>
-__device__ __forceinline__ void pwi_issue(const PwArgs& a, int tile, int n0, int kc, char* stage, int wave, int lane) {
-  constexpr int ACT_INSTR = PwSmemI::ACT / 1024;
-#pragma unroll
-  for (int i = 0; i < ACT_INSTR / 8; ++i) {
-    const int ins = wave + 8 * i;
-    const int slot = ins * 64 + lane;
-    const int px = slot >> 3, v = (slot & 7) ^ ((px >> 1) & 7);  // conflict-free B reads (16-lane quarters)
-    const int gp = min(tile * 128 + px, a.P - 1);
-    dma16(pwi_act_src<LOADER>(a, gp, kc, v), stage + ins * 1024);
-  }
+__device__ __forceinline__ void pwi_issue(const PwArgs& a, PwAct<LOADER>& act, int n0, int kc, char* stage, int wave, int lane) {
+  act.issue(a, kc, stage, wave);
   const int ks = a.K / 32;
 #pragma unroll
   for (int i = 0; i < PwSmemIN<NT>::WGT / 1024 / 8; ++i) {
     const int f = wave + 8 * i;  // row tile f / 4; f % 4: hi k0, hi k1, lo k0, lo k1
     const int mt = n0 / 32 + (f >> 2), sk = 2 * kc + (f & 1);
     const char* plane = (f & 2) ? (const char*)a.wfrag_lo : (const char*)a.wfrag;
-    dma16(plane + (((size_t)mt * ks + sk) * 64 + lane) * 16, stage + PwSmemI::ACT + f * 1024);
+    dma16s(plane + ((size_t)mt * ks + sk) * 1024, lane * 16, stage + PwSmemI::ACT + f * 1024);
   }
 }
 
@@ -164,14 +139,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NT == 64 ? 
 #pragma unroll
     for (int g = 0; g < 4; ++g) corr[t][g] = *(const intx4*)((const int*)a.bias + n0 + 32 * (hf * RT + t) + 8 * g + 4 * h);
 
-  pwi_issue<NT, LOADER>(a, tile, n0, 0, st0, wave, lane);
-  if (nk > 1) pwi_issue<NT, LOADER>(a, tile, n0, 1, st1, wave, lane);
+  PwAct<LOADER> act;
+  act.init(a, tile, n0, wave, lane);
+  pwi_issue<NT, LOADER>(a, act, n0, 0, st0, wave, lane);
+  if (nk > 1) pwi_issue<NT, LOADER>(a, act, n0, 1, st1, wave, lane);
   auto step = [&](int kc, const char* cur, char* refill) {
     const int ahead = min(nk - 1 - kc, 1);  // stages issued after kc still in flight
     if (ahead == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(S::DMA_PER_WAVE) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();
-    if (kc + 2 < nk) pwi_issue<NT, LOADER>(a, tile, n0, kc + 2, refill, wave, lane);
+    if (kc + 2 < nk) pwi_issue<NT, LOADER>(a, act, n0, kc + 2, refill, wave, lane);
     pwi_compute<NT, LOADER>(cur, pg, hf, lane, acc);
   };
   for (int kc = 0; kc < nk; kc += 3) {
