@@ -46,7 +46,8 @@ __global__ __launch_bounds__(256) void k_bits(const int16_t* q, const void* scal
 
 // Zeroes two ranges of 16-byte units (the two tensors of a context's state).  Bound by
 // launch and memory: both state tensors of a 1080p frame (21 MB) took 10.2 + 5.1 us as two
-// launches of 4-byte stores.
+// launches of 4-byte stores, 10.0 here (2,048 workgroups; 512 12.9 us, 1,024 10.8, one store per
+// thread 13.4, non-temporal 9.2 but the kernels that read the state next lose more).
 __global__ __launch_bounds__(256) void k_fill_zero(intx4* p0, size_t n0, intx4* p1, size_t n1) {
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n0 + n1; i += (size_t)gridDim.x * 256)
     (i < n0 ? p0[i] : p1[i - n0]) = intx4{};
@@ -59,7 +60,8 @@ __global__ __launch_bounds__(256) void k_fill_zero(intx4* p0, size_t n0, intx4* 
 // are 16-byte aligned: P a multiple of 8 and an aligned buffer).  C is a
 // multiple of 64.  Element by element (each lane striding through the other
 // layout) the context feature of a 1080p frame (16.7 MB each way) took 58 us
-// in and 87 us out, the tiles take 7.8 us (4.3 TB/s); at 4K 490 against 25 us.
+// in and 87 us out, the tiles take 7.8 us (4.3 TB/s), 8.2 us with the latent's 4.2 MB in the
+// same launch (13.1 as two); at 4K 490 against 25 us.
 constexpr int kTrLd = 64 + 2;  // LDS row stride (elements): rows one bank apart
 
 struct StateCopy {
