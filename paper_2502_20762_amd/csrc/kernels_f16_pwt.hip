@@ -10,8 +10,8 @@
 // registers per lane and 64 KiB of LDS leave room for two workgroups per CU: one's
 // waits and stores run beside the other's MFMAs.  (One workgroup of 256 rows x 256
 // pixels per CU, with 4 or with 8 waves, was slower: 50 and 44 us against 40 for
-// K = 512, N = 1024 at 1080p.)  The sums start at the bias (fp32); the results are
-// rounded to fp16 once, parked in LDS and stored as 16-byte vectors.
+// K = 512, N = 1024 at 1080p.)  The sums are fp32; the results are rounded to fp16
+// once, parked in LDS and stored as 16-byte vectors.
 #include <type_traits>
 #include <utility>
 
@@ -22,8 +22,8 @@ namespace nc {
 
 namespace {
 
-template <int LOADER, int EPI, int RT, int PG>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RT * PG > 8 ? 1 : 2))) void k_pwt_f16(PwArgs a) {
+template <int LOADER, int EPI, int RT, int PG, bool BIAS_FIRST>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_pwt_f16(PwArgs a) {
   constexpr int NR = 128 * RT, NPX = 32 * PG;  // rows and pixels of a workgroup
   constexpr int STAGE = NPX * 128;             // activation bytes of a stage
   constexpr int OUT = EPI == EP_GATE ? NR / 2 : NR;  // stored channels
@@ -85,20 +85,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RT * PG > 8
       for (int t = 0; t < RT; ++t)
         qa[b][ks][t] = *(const half8*)(wf + ((size_t)t * (a.K / 16) + 4 * kc + ks) * 1024 + lane * 16);
   };
-  floatx16 acc[RT][PG];
-  {
-    const float* bp = (const float*)a.bias + n0 + 32 * RT * wave + 4 * h;
+  // The sums of the model at C = 256 start at the bias, at other widths it comes last: the
+  // order these layers have always had, so that a frame coded with one kernel has the
+  // same values with another.  A bias that comes last is held from the start where the
+  // registers allow (loaded at the end it costs 0.5 us of a 6 us launch).
+  const float* const bp = (const float*)a.bias + n0 + 32 * RT * wave + 4 * h;
+  constexpr bool HELD = BIAS_FIRST || RT * PG < 8;
+  floatx4 bias[RT][4];
+  auto load_bias = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const floatx4 bv = *(const floatx4*)(bp + 32 * t + 8 * q);
+      for (int q = 0; q < 4; ++q) bias[t][q] = *(const floatx4*)(bp + 32 * t + 8 * q);
+  };
+  if constexpr (HELD) load_bias();
+  floatx16 acc[RT][PG];
 #pragma unroll
-        for (int g = 0; g < PG; ++g)
+  for (int t = 0; t < RT; ++t)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) acc[t][g][4 * q + e] = bv[e];
-      }
-  }
+    for (int g = 0; g < PG; ++g)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[t][g][i] = BIAS_FIRST ? bias[t][i / 4][i % 4] : 0.f;
   // B fragment of k-step ks, group g: pixel 32 g + n, vector 2 ks + h
   int bo[4];
 #pragma unroll
@@ -140,6 +147,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RT * PG > 8
   for (int kc = 0; kc < nk; kc += 2) {
     stage(kc, std::integral_constant<int, 0>{});
     if (kc + 1 < nk) stage(kc + 1, std::integral_constant<int, 1>{});
+  }
+  if constexpr (!BIAS_FIRST) {
+    if constexpr (!HELD) load_bias();
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int g = 0; g < PG; ++g)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[t][g][i] += bias[t][i / 4][i % 4];
   }
   lds_barrier();  // every wave is done reading the stages
 
@@ -235,7 +251,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RT * PG > 8
 
 template <int LOADER, int EPI, int RT, int PG>
 hipError_t go(const PwArgs& a, int wgs, hipStream_t st) {
-  launch(k_pwt_f16<LOADER, EPI, RT, PG>, dim3((wgs + 7) / 8 * 8), dim3(256), st, a);
+  const dim3 grid((wgs + 7) / 8 * 8);
+  if constexpr (EPI == EP_REC || EPI == EP_UP || EPI == EP_NHWC) {
+    if (EPI == EP_REC ? a.K == 256 : a.Cdst == 256) {
+      launch(k_pwt_f16<LOADER, EPI, RT, PG, true>, grid, dim3(256), st, a);
+      return hipGetLastError();
+    }
+  }
+  launch(k_pwt_f16<LOADER, EPI, RT, PG, false>, grid, dim3(256), st, a);
   return hipGetLastError();
 }
 
