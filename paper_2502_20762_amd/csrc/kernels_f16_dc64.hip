@@ -305,50 +305,112 @@ __device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b
 #pragma unroll
       for (int c = 0; c < 2; ++c)
         if (c < nfrag(s)) qa[s][c] = afrag(s, c);
-    // the lane's band reads: column i (half 0) or 9 - i (half 1) of a row, its
-    // channel pair's dword; rows of odd index at va ^ 64
+    // The lane's outputs k = 0 .. 3 of a row, at tile column x(k), and its band reads.
+    // C < 256: x = k + 4 half, six consecutive columns, the nine taps of an output row by row
+    // and left to right (fp32 fma).
+    // C = 256: the taps of a row are two dot2 pairs, (first, middle) and (0, last); the sums
+    // of the 8 x 16 tiles' kernel run from the left in the left half of a 16-column group and
+    // from the right in its right half, so here a tile at an even tile column runs from the
+    // left (dir = 0) and the others from the right, and a frame has the same values on
+    // either tile.  k = 0 is the column next to the ring (0 or 7), which is known last, k = 1 .. 3
+    // the three others in that direction: role 0 (the half the direction starts from) x(k) = 0
+    // .. 3 from its side, role 1 the far column first.
+    constexpr bool DOT2 = C == 256;
+    const int dir = txi & 1, role = half ^ dir;
+    auto band_off = [&](int col) __attribute__((always_inline)) {
+      return r0 * BROW + col * 128 + (((cp >> 2) ^ usw(0, col)) << 4) + (cp & 3) * 4;
+    };
+    // columns of k >= 1 (DOT2: lane order 1 .. 5) or of all outputs (0 .. 5); rows of odd index at va ^ 64
     int va[TW / 2 + 2];
 #pragma unroll
     for (int i = 0; i < TW / 2 + 2; ++i) {
-      const int col = half ? TW + 1 - i : i;
-      va[i] = r0 * BROW + col * 128 + (((cp >> 2) ^ usw(0, col)) << 4) + (cp & 3) * 4;
+      const int from = role ? 3 + i : i;  // counted from the side the direction starts at
+      va[i] = band_off(DOT2 ? (dir ? BW - 1 - from : from) : 4 * half + i);
     }
-    // taps of a row as dot2 pairs (mirrored for half 1): (A0, A1) . (z[k],
-    // z[k + 1]) and (0, A2) . (z[k + 1], z[k + 2]) in the lane's column order
+    int ve[3];  // DOT2: the columns of k = 0
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const int from = role ? 7 + j : j;
+      ve[j] = band_off(dir ? BW - 1 - from : from);
+    }
+    // taps of a row as dot2 pairs in the lane's column order
     half2 W0a[3], W0b[3], W1a[3], W1b[3];
 #pragma unroll
     for (int ky = 0; ky < 3; ++ky) {
-      const half2 l = half ? wt[3 * ky + 2] : wt[3 * ky], m = wt[3 * ky + 1], r = half ? wt[3 * ky] : wt[3 * ky + 2];
+      const half2 l = dir ? wt[3 * ky + 2] : wt[3 * ky], m = wt[3 * ky + 1], r = dir ? wt[3 * ky] : wt[3 * ky + 2];
       W0a[ky] = half2{l[0], m[0]};
       W0b[ky] = half2{(f16)0.f, r[0]};
       W1a[ky] = half2{l[1], m[1]};
       W1b[ky] = half2{(f16)0.f, r[1]};
     }
-    // band rows (from row r0 on) as tap pairs of one channel: P0[y][i] =
-    // (z[y][i], z[y][i + 1]) of the pair's first channel, P1 of its second
-    half2 P0[G::RPW + 2][TW / 2 + 1], P1[G::RPW + 2][TW / 2 + 1];
+    // band rows (from row r0 on).  DOT2: tap pairs of one channel, P0[y][i] = columns (i, i +
+    // 1) of k >= 1, Q0[y][j] = columns (j, j + 1) of k = 0, for the pair's first channel, P1
+    // and Q1 for its second; else V[y][i] = the channel pair at column i
+    half2 P0[G::RPW + 2][TW / 2 + 1], P1[G::RPW + 2][TW / 2 + 1], Q0[G::RPW + 2][2], Q1[G::RPW + 2][2];
+    half2 V[G::RPW + 2][TW / 2 + 2];
     half2 out[G::RPW][TW / 2];
-    auto load_row = [&](int y, int i0) __attribute__((always_inline)) {
-      uint32_t vr[TW / 2 + 2];
+    auto band_at = [&](int y, int off) __attribute__((always_inline)) {
+      return *(const uint32_t*)(band + y * BROW + ((y & 1) ? off ^ 64 : off));
+    };
+    // what the outputs k >= 1 and k = 0 of a row need of band row y
+    auto load_row = [&](int y, bool rest, bool edge) __attribute__((always_inline)) {
+      if constexpr (!DOT2) {
 #pragma unroll
-      for (int i = 0; i < TW / 2 + 2; ++i)
-        if (i >= i0) vr[i] = *(const uint32_t*)(band + y * BROW + ((y & 1) ? va[i] ^ 64 : va[i]));
+        for (int i = 0; i < TW / 2 + 2; ++i) V[y][i] = __builtin_bit_cast(half2, band_at(y, va[i]));
+      } else {
+        auto lo = [](uint32_t a, uint32_t b) { return __builtin_bit_cast(half2, __builtin_amdgcn_perm(b, a, 0x05040100u)); };
+        auto hi = [](uint32_t a, uint32_t b) { return __builtin_bit_cast(half2, __builtin_amdgcn_perm(b, a, 0x07060302u)); };
+        uint32_t vr[TW / 2 + 2], er[3];
+        if (rest)
 #pragma unroll
-      for (int i = 0; i < TW / 2 + 1; ++i)
-        if (i >= i0) {
-          P0[y][i] = __builtin_bit_cast(half2, __builtin_amdgcn_perm(vr[i + 1], vr[i], 0x05040100u));
-          P1[y][i] = __builtin_bit_cast(half2, __builtin_amdgcn_perm(vr[i + 1], vr[i], 0x07060302u));
-        }
+          for (int i = 1; i < TW / 2 + 2; ++i) vr[i] = band_at(y, va[i]);
+        if (edge)
+#pragma unroll
+          for (int j = 0; j < 3; ++j) er[j] = band_at(y, ve[j]);
+        if (rest)
+#pragma unroll
+          for (int i = 1; i < TW / 2 + 1; ++i) {
+            P0[y][i] = lo(vr[i], vr[i + 1]);
+            P1[y][i] = hi(vr[i], vr[i + 1]);
+          }
+        if (edge)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            Q0[y][j] = lo(er[j], er[j + 1]);
+            Q1[y][j] = hi(er[j], er[j + 1]);
+          }
+      }
     };
     // one output (row r, step k) of the channel pair
     auto dw_out = [&](int r, int k) __attribute__((always_inline)) {
       float a0 = bias0, a1 = bias1;
+      if constexpr (DOT2) {
 #pragma unroll
-      for (int ky = 0; ky < 3; ++ky) {
-        a0 = __builtin_amdgcn_fdot2(W0a[ky], P0[r + ky][k], a0, false);
-        a0 = __builtin_amdgcn_fdot2(W0b[ky], P0[r + ky][k + 1], a0, false);
-        a1 = __builtin_amdgcn_fdot2(W1a[ky], P1[r + ky][k], a1, false);
-        a1 = __builtin_amdgcn_fdot2(W1b[ky], P1[r + ky][k + 1], a1, false);
+        for (int y = r; y < r + 3; ++y) {
+          a0 = __builtin_amdgcn_fdot2(W0a[y - r], k ? P0[y][k] : Q0[y][0], a0, false);
+          a0 = __builtin_amdgcn_fdot2(W0b[y - r], k ? P0[y][k + 1] : Q0[y][1], a0, false);
+          a1 = __builtin_amdgcn_fdot2(W1a[y - r], k ? P1[y][k] : Q1[y][0], a1, false);
+          a1 = __builtin_amdgcn_fdot2(W1b[y - r], k ? P1[y][k + 1] : Q1[y][1], a1, false);
+        }
+      } else {
+        // even rows, odd columns: the last tap's sum is rounded to fp16 by the fma itself, at
+        // the others to fp32 and then to fp16 (fixed here, so that it does not depend on the
+        // compiler's choice of instructions)
+        const bool fused = r % 2 == 0 && k % 2 == 1;
+#pragma unroll
+        for (int t = 0; t < (fused ? 8 : 9); ++t) {
+          const half2 ww = wt[t], zz = V[r + t / 3][k + t % 3];
+          a0 = fmaf((float)ww[0], (float)zz[0], a0);
+          a1 = fmaf((float)ww[1], (float)zz[1], a1);
+        }
+        if (fused) {
+          asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,1,0]\n\t"
+              "v_fma_mixhi_f16 %0, %1, %2, %4 op_sel:[1,1,0] op_sel_hi:[1,1,0]"
+              : "=&v"(out[r][k])
+              : "v"(wt[8]), "v"(V[r + 2][k + 2]), "v"(a0), "v"(a1));
+          return;
+        }
+        asm("" : "+v"(a0), "+v"(a1));
       }
       out[r][k] = half2{(f16)a0, (f16)a1};
     };
@@ -369,11 +431,11 @@ __device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b
       }
     };
     auto dw_rows = [&]() __attribute__((always_inline)) {
-      load_row(0, 0);
-      load_row(1, 0);
+      load_row(0, true, true);
+      load_row(1, true, true);
 #pragma unroll
       for (int r = 0; r < G::RPW; ++r) {
-        load_row(r + 2, 0);
+        load_row(r + 2, true, true);
 #pragma unroll
         for (int k = 0; k < TW / 2; ++k) dw_out(r, k);
       }
@@ -389,11 +451,11 @@ __device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b
       // and the residual
       read_res();
       if constexpr (G::RPW == TH) {
-        load_row(1, 1);
-        load_row(2, 1);
+        load_row(1, true, false);
+        load_row(2, true, false);
 #pragma unroll
         for (int r = 1; r <= TH - 2; ++r) {
-          load_row(r + 2, 1);
+          load_row(r + 2, true, false);
 #pragma unroll
           for (int k = 1; k < TW / 2; ++k) dw_out(r, k);
         }
@@ -444,17 +506,17 @@ __device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b
         if (ro[i] >= 0) *(half8*)(band + ro[i]) = rv[i];
       if constexpr (G::RPW == TH) {
         // the outputs that read the ring
-        load_row(0, 0);
-        load_row(1, 0);
-        load_row(2, 0);
+        load_row(0, true, true);
+        load_row(1, true, true);
+        load_row(2, true, true);
 #pragma unroll
         for (int k = 0; k < TW / 2; ++k) dw_out(0, k);
 #pragma unroll
         for (int r = 1; r <= TH - 2; ++r) {
-          load_row(r + 2, 0);
+          load_row(r + 2, r >= TH - 3, true);
           dw_out(r, 0);
         }
-        load_row(TH + 1, 0);
+        load_row(TH + 1, true, true);
 #pragma unroll
         for (int k = 0; k < TW / 2; ++k) dw_out(TH - 1, k);
       } else {
@@ -465,21 +527,23 @@ __device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b
     // the band has been read (by every wave of its group) before a goes over it
     if constexpr (G::RW > 1) lds_barrier();
     if (bi < 3 * C / 4) *(floatx4*)(smem + G::OBIAS + 16 * bi) = bv;
-    // output (row r, step k): column x = k (half 0) or 7 - k (half 1), a's
-    // fragment (group r / 4, k-step 4 cg + cp / 8), lane slot 8 (r % 4) + x +
-    // 32 kh, kh = (cp / 4) % 2 (bslot of it: kk = k, side = half), elements
-    // 2 (cp % 4), + 1
+    // output (row r, step k): column x(k), a's fragment (group r / 4, k-step 4 cg + cp /
+    // 8), lane slot 8 (r % 4) + x + 32 kh, kh = (cp / 4) % 2 (bslot of it: side = half, kk
+    // = x or 7 - x), elements 2 (cp % 4), + 1
     const int kh = (cp >> 2) & 1;
     int fo[2];
 #pragma unroll
     for (int par = 0; par < 2; ++par)
       fo[par] = cg * REG + (cp >> 3) * XF + (cp & 3) * 4 + (32 * kh + 4 * ((half + 2 * par + 2 * kh) & 3)) * 16;
+    int kk[TW / 2];
+#pragma unroll
+    for (int k = 0; k < TW / 2; ++k) kk[k] = 16 * (DOT2 ? (role ? (4 - k) & 3 : k) : (half ? 3 - k : k));
 #pragma unroll
     for (int r = 0; r < G::RPW; ++r) {
       const int rr = r0 + r;
 #pragma unroll
       for (int k = 0; k < TW / 2; ++k)
-        *(half2*)(smem + fo[r & 1] + (rr >> 2) * 4 * XF + ((rr >> 1) & 1) * 256 + 16 * k) = out[r][k];
+        *(half2*)(smem + fo[r & 1] + kk[k] + (rr >> 2) * 4 * XF + ((rr >> 1) & 1) * 256) = out[r][k];
     }
   }
   lds_barrier();  // a and the biases complete; every wave holds its residual
@@ -506,9 +570,9 @@ __device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b
     }
   };
   // Hand-off of round r: the hidden values as pw2 B fragments (the pw2 weights
-  // are packed in the accumulators' register order).  LeakyReLU: max(h, 0.1 h)
-  // of the fp16-rounded value, in packed fp16.  Gated: WSiLU(h1) = h1
-  // sigmoid(4 h1) rounded to fp16, then g = WSiLU(h1) h2 rounded to fp16.
+  // are packed in the accumulators' register order).  LeakyReLU: C = 64 and 128 in fp32,
+  // rounded to fp16 once; C = 256 max(h, 0.1 h) of the fp16-rounded value, in packed fp16.
+  // Gated: WSiLU(h1) = h1 sigmoid(4 h1) rounded to fp16, then g = WSiLU(h1) h2 rounded to fp16.
   auto handoff = [&](int r) __attribute__((always_inline)) {
 #pragma unroll
     for (int g = 0; g < G::G1; ++g)
@@ -527,17 +591,40 @@ __device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b
         } else {
 #pragma unroll
           for (int c = 0; c < G::C1; ++c) {
-            half8 hv, gv;
+            half8 gv;
+            if constexpr (C < 256) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) hv[e] = (f16)acc[c][g][8 * u + e];
-            const half8 sl = hv * (f16)0.1f;
+              for (int e = 0; e < 8; ++e) gv[e] = (f16)leaky(acc[c][g][8 * u + e]);
+            } else {
+              half8 hv;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) gv[e] = __builtin_fmaxf16(hv[e], sl[e]);
+              for (int e = 0; e < 8; ++e) hv[e] = (f16)acc[c][g][8 * u + e];
+              const half8 sl = hv * (f16)0.1f;
+#pragma unroll
+              for (int e = 0; e < 8; ++e) gv[e] = __builtin_fmaxf16(hv[e], sl[e]);
+            }
             const int k = 2 * G::C1 * wave + 2 * c + u;
             *(half8*)(smem + (r ? G::h1_off(g, k) : G::h0_off(g, k)) + myslot) = gv;
           }
         }
       }
+  };
+  // The residual enters the pw2 sums through the identity (the two 32 x 16 halves as A,
+  // exact products), at C = 256 before the hidden layer, at C = 64 and 128 after it.
+  auto add_res = [&]() __attribute__((always_inline)) {
+    const int row = lane & 31;
+    half8 e0, e1;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      e0[e] = (f16)(row == 8 * h + e ? 1.f : 0.f);
+      e1[e] = (f16)(row == 16 + 8 * h + e ? 1.f : 0.f);
+    }
+#pragma unroll
+    for (int c = 0; c < G::T2; ++c)
+#pragma unroll
+      for (int g = 0; g < G::G2; ++g)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) acc[c][g] = mfma_f16(q ? e1 : e0, res[c][g][q], acc[c][g]);
   };
   auto ngroup = [](int t) constexpr { return t < N1 ? G::G1 : G::G2; };
   // B fragment g of the wave at step t
@@ -576,25 +663,10 @@ __device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b
       // at issue)
       if constexpr (G::R == 2) lds_barrier();
       handoff(G::R - 1);
-      // the pw2 accumulators start from the bias; the residual enters first,
-      // through the identity (the two 32 x 16 halves as A, exact products)
+      // the pw2 accumulators start from the bias
 #pragma unroll
       for (int c = 0; c < G::T2; ++c) init_acc(c, 2 * C + 32 * (tile0 + c), G::G2);
-      {
-        const int row = lane & 31;
-        half8 e0, e1;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          e0[e] = (f16)(row == 8 * h + e ? 1.f : 0.f);
-          e1[e] = (f16)(row == 16 + 8 * h + e ? 1.f : 0.f);
-        }
-#pragma unroll
-        for (int c = 0; c < G::T2; ++c)
-#pragma unroll
-          for (int g = 0; g < G::G2; ++g)
-#pragma unroll
-            for (int q = 0; q < 2; ++q) acc[c][g] = mfma_f16(q ? e1 : e0, res[c][g][q], acc[c][g]);
-      }
+      if constexpr (C == 256) add_res();
       lds_barrier();
       start_b(t);
     }
@@ -619,6 +691,7 @@ __device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b
     __builtin_amdgcn_sched_barrier(0);
   };
   unrolled(step, std::make_integer_sequence<int, NT>{});
+  if constexpr (C < 256) add_res();
 
   lds_barrier();  // every wave is done reading the hidden layer
   // ---- the output, rounded to fp16 once, into the interior of the bands:

@@ -1,8 +1,9 @@
 """fp16 results stay what they were: an fp16 stream only decodes to what its encoder saw if both run the
 same sums and roundings, also when one of them is an older build.  golden/fp16_digests.json
 holds CRC-32s of one P-frame's symbols, rate and state and of a decoded frame, computed on an
-MI355X with the kernels of commit d8d944d (one launch per block and chained alike), at
-sizes on both sides of the rules that choose tiles.  Bit for bit: no tolerance."""
+MI355X with the kernels of commit d8d944d (one launch per block and chained alike), for every
+width and block form, at sizes on both sides of the rules that choose tiles.  Bit for bit: no
+tolerance.  Then infinities: a depthwise whose window holds one gives infinity, not NaN."""
 import json
 import os
 import zlib
@@ -48,3 +49,27 @@ def test_results_are_bit_identical(d):
                "feat_decoded": crc(f2)}
         assert got == {k: d[k] for k in got}, "chains" if chains else "one launch per block"
 
+
+@pytest.mark.parametrize("C", [64, 128])
+def test_infinite_activations_stay_infinite(C):
+    # every weight and bias positive; one infinite value in the context reaches the block through
+    # the fuse conv, so the block's output is +inf in the 8 pixels around it and finite elsewhere (at
+    # the pixel itself the residual is added through an identity matrix: 0 * inf)
+    H, W = 80, 144
+    flat = np.abs(synth.make_weights(C, 1, 1))
+    flat = np.where(flat == 0, np.float32(2.0 ** -14), flat)
+    feat = torch.zeros((C, H // 8, W // 8), dtype=torch.float16, device=DEV)
+    feat[3, 4, 7] = float("inf")
+    c = Codec(H, W, C, 1, 1, "fp16", flat, device=DEV)
+    c.set_state(feat, torch.zeros((C, H // 16, W // 16), dtype=torch.float16, device=DEV))
+    c.decode(torch.zeros((C, H // 16, W // 16), dtype=torch.int16, device=DEV))
+    f, _ = c.get_state()
+    torch.cuda.synchronize()
+    want = torch.zeros((H // 8, W // 8), dtype=torch.bool)
+    want[3:6, 6:9] = True
+    f = f.cpu()
+    assert not f[:, 4, 7].isfinite().any()
+    want[4, 7] = False
+    f[:, 4, 7] = 0
+    assert not f.isnan().any()
+    assert torch.equal(f == float("inf"), want.expand(C, -1, -1))
