@@ -366,17 +366,21 @@ ncodec_status ncodec_graph_enable(ncodec_ctx* ctx, int32_t enable);
  * neighbouring tiles through memory.  The shortest run that does is two blocks
  * at C = 256, four for the small models and the integer gated form.  Tiles are 8 x
  * 8 pixels, two per CU, or 8 x 16 for fp16 LeakyReLU blocks at C = 256 on
- * frames of more than 320 tiles of 8 x 8.  Used only where every tile fits the
+ * frames of more than 320 tiles of 8 x 8.  Used where every tile fits the
  * device at once (checked once per context with the occupancy API; 510 tiles of
  * 8 x 8 or 255 of 8 x 16 at 1080p), on the fp16 path below C = 256 up to 256
  * tiles; otherwise, and with enable = 0, one launch per block.  Results are
- * identical either way.  On by default.  Chains of different streams of a
- * process are ordered one after the other unless they are small (at most 64
- * tiles each).  A tile waits at most about 0.1 s for a neighbour (a case that
- * needs another process's kernel holding CUs for that long); a wait that gives up
- * leaves the block outputs wrong and is reported by ncodec_block_chain_status.
+ * identical either way, also where a launch finds part of the device taken
+ * by another stream's kernel or another process: its workgroups wait a few
+ * milliseconds for the rest, then those that are there run the blocks one after
+ * the other (a slow launch, the same results).  On by default.  Chains of
+ * different streams of a process are ordered one after the other unless they are
+ * small (at most 64 tiles each).
+ * enable = NCODEC_CHAINS_SEALED: every chain launch takes the way of one without
+ * room for its tiles (for tests of it).
  * Changing the setting drops captured graphs (the next graph call captures
  * again).  Errors: EINVAL for a NULL ctx, EHIP. */
+#define NCODEC_CHAINS_SEALED 0x5ea1ed
 ncodec_status ncodec_block_chains(ncodec_ctx* ctx, int32_t enable);
 
 /* *in_use = 1 if this context's DC blocks run as chains (enabled, a path, width

@@ -375,10 +375,9 @@ struct Layout {
   // state and intermediates (offsets from the workspace base)
   size_t feat[2], yhat[2], ed, zA, zB, y, partials, zpad, spare_bits;
   size_t dwa = 0, hid = 0;  // wide blocks (C > 256): depthwise output, hidden layer
-  // chains of blocks in one launch (C <= 256): one progress word per tile
-  // (zero at creation; every launch adds the same count to all) and a
-  // timeout flag
-  size_t chain_flags = 0, chain_status = 0;
+  // chains of blocks in one launch (C <= 256): one progress word per tile, two slots for the
+  // launch's count of its workgroups (all zero at creation; chain_sync.hpp) and a timeout flag
+  size_t chain_flags = 0, chain_status = 0, chain_slots = 0;
   // entropy coder: scale indices, symbols, per-stream scratch, lengths,
   // offsets, status words, byte count
   size_t kmap, qtmp, rscratch, rlens, rerrs, rcount;
@@ -717,6 +716,7 @@ bool build_layout(const ncodec_config& cfg, const float* w, Image& img, Layout& 
     const size_t tiles = (size_t)((cfg.height / 8 + 7) / 8) * ((cfg.width / 8 + 7) / 8);
     L.chain_flags = alloc(tiles * 4);
     L.chain_status = alloc(4);
+    L.chain_slots = alloc(2 * sizeof(ChainSlot));
   }
   const size_t P32 = P16 / 4;
   // rate partial sums: the prior's (tiles x passes); with the two-step model
@@ -783,7 +783,7 @@ struct ncodec_ctx {
   GraphSlot graphs[2][2];  // [decode][cur]
   // consecutive blocks as one chain launch (when every tile fits the device
   // at once; chain_fit: -1 not yet checked, 0 no, 1 yes)
-  bool chains = true;
+  bool chains = true, seal_chains = false;  // seal_chains: NCODEC_CHAINS_SEALED
   int chain_fit = -1;
   // Parallel coding (Fig. 6; supplementary "Parallel Coding"): the coded
   // calls run the entropy coder (encode) or the feature extractor (decode) on
@@ -1102,6 +1102,8 @@ hipError_t run_blocks(ncodec_ctx* ctx, const std::vector<BlockDev>& blocks, cons
     ca.nb = m;
     ca.flags = ctx->p<int>(ctx->L.chain_flags);
     ca.status = ctx->p<int>(ctx->L.chain_status);
+    ca.slots = ctx->p<ChainSlot>(ctx->L.chain_slots);
+    ca.seal = ctx->seal_chains ? 1 : 0;
     const bool fuse = down && !ctx->is_int() && ctx->cfg.channels == 256 && k0 + m == n;
     if (fuse) {
       ca.down_w = ctx->p(down->w);
@@ -2048,7 +2050,8 @@ ncodec_status ncodec_graph_enable(ncodec_ctx* ctx, int32_t enable) {
 ncodec_status ncodec_block_chains(ncodec_ctx* ctx, int32_t enable) {
   ncodec_status st = enter(ctx);
   if (st) return st;
-  if (ctx->chains != (enable != 0)) {
+  const bool seal = enable == NCODEC_CHAINS_SEALED;
+  if (ctx->chains != (enable != 0) || ctx->seal_chains != seal) {
     // captured graphs hold the other launch sequence: capture again on next use
     NC_HIP(ctx, hipStreamSynchronize(ctx->stream), "block_chains");
     for (auto& row : ctx->graphs)
@@ -2059,6 +2062,7 @@ ncodec_status ncodec_block_chains(ncodec_ctx* ctx, int32_t enable) {
       }
   }
   ctx->chains = enable != 0;
+  ctx->seal_chains = seal;
   return NCODEC_OK;
 }
 

@@ -9,6 +9,7 @@
 #include <string>
 
 #include "../../include/ncodec.h"
+#include "chain_sync.hpp"
 
 namespace nc {
 
@@ -118,15 +119,18 @@ struct BlockArgs {
 };
 
 // A run of DC blocks in one launch (the chain kernels):
-// blk[b].src = blk[b - 1].dst; flags: one int per tile, zero at workspace
-// creation and left equal across tiles by every launch; status: set to 1 if a
-// wait for a neighbouring tile timed out.
+// blk[b].src = blk[b - 1].dst; flags: one progress word per tile, slots: two, all zero at
+// workspace creation (chain_sync.hpp); seal: the launch goes the way of one whose tiles
+// are not all on the device; status: set to 1 if a wait gave up.
 constexpr int kMaxChain = 16;
+static_assert(kMaxChain <= (int)kChainStep, "a launch's progress stays below the next one's base");
 struct DcChainArgs {
   BlockArgs blk[kMaxChain];
   int nb;
+  int seal;
   int* flags;
   int* status;
+  ChainSlot* slots;
   // fp16 chains at C = 256 only: when down_w is set, the last block's output stays in LDS
   // and feeds the 2x2 stride-2 downsample of the tile instead (down_w: its
   // weight fragments, K = 4C, N = C; down_b: C fp32 biases; down_y: the 1/16

@@ -32,6 +32,7 @@
 #include <utility>
 
 #include "common.hpp"
+#include "dc_chain.hpp"
 #include "internal.hpp"
 
 namespace nc {
@@ -52,8 +53,10 @@ constexpr int REG = BAND_INSTR * 1024;
 constexpr int OA = 4 * REG;                        // a: [group 4][k-step 16] fragments, later the round-1 hidden layer
 constexpr int OBIAS = OA + 64 * XF;                // pw1 biases (2C fp32), then pw2 biases (C fp32)
 constexpr int SMEM = OBIAS + 3 * C * 4;
+constexpr int SYNC = OA - 16;                      // a word no one else uses once the first band is in
 static_assert(SMEM <= 160 * 1024, "fits the LDS of a CU");
 static_assert(64 * XF <= OA && TH * TW * C * 2 <= OA, "the round-0 hidden layer and the parked output fit over the bands");
+static_assert(64 * XF <= SYNC && BH * BW * 128 <= REG - 16, "the chains' word lies behind the last band");
 // direct load holding the last unit of band row y (loads land in order)
 constexpr int band_row_load(int y) { return (8 * (BW * y + BW - 1) + 7) / 64; }
 static_assert(band_row_load(BH - 1) == BAND_INSTR - 1, "band geometry");
@@ -93,29 +96,12 @@ __device__ __forceinline__ void unrolled(F& f, std::integer_sequence<int, T...>)
 // into the next block's band interior, so between blocks only the ring of the
 // band (the neighbours' edge pixels) moves through memory: a block other than
 // the last stores only the tile's 44 edge pixels, then publishes its progress
-// in flags[tile]; the next block waits until every neighbouring tile has
+// in its word; the next block waits until every neighbouring tile has
 // published that block, then reads its ring (edge stores, ring loads and the
 // progress words are device-coherent accesses; the stores' acknowledgements
-// are awaited before the word is written).  Every tile of the grid must be
-// resident at once (one workgroup per CU; the host checks the occupancy), and
-// each wait gives up after a bounded time, recording it in *status.  flags
-// hold a running count: every launch adds nb - 1 to each tile's word, so all
-// words are equal between launches and a launch reads its base from its own
-// tile's word.
-
-// 16-byte device-coherent accesses (the sc1 policy of device-scope atomics:
-// past this XCD's L2 to the device's point of coherence), whole 128-byte lines
-// per 8 lanes, without a cache-wide fence (a fence would write back or drop
-// the whole L2, weights included).  The load's result may only be used after
-// wait_coherent() on it.
-__device__ __forceinline__ half8 load_coherent16(const f16* p) {
-  half8 v;
-  asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory");
-  return v;
-}
-__device__ __forceinline__ void store_coherent16(f16* p, half8 v) {
-  asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
-}
+// are awaited before the word is written).  The host launches a chain where the device
+// holds every tile of the grid at once (one workgroup per CU); a launch that finds itself
+// without room for them all runs block by block with those that are there (chain_sync.hpp).
 
 // The 2x2 stride-2 downsample of a tile's block output, parked in LDS (row =
 // tile pixel, 8-byte unit u of the row at u ^ (p & 15)): output rows
@@ -189,12 +175,11 @@ __device__ __forceinline__ void dc128_down(const char* smem, const DcChainArgs& 
 }
 
 // One block of a tile (FIRST: its band comes whole from a.src; LAST: its
-// output goes whole to a.dst, or with ca->down_w set through the fused
+// output goes whole to a.dst, or with ca->down_w set, and down, through the fused
 // downsample to ca->down_y; otherwise the chain's ring and edge exchange).
 template <bool CHAIN, bool FIRST, bool LAST>
-__device__ __forceinline__ void dc128_block(char* smem, const BlockArgs& a, int b, int tile, int tiles_x, int tiles_y,
-                                            int wave0, int base, int* flags, int* status,
-                                            const DcChainArgs* ca) {
+__device__ __forceinline__ bool dc128_block(char* smem, const BlockArgs& a, int b, int tile, int tiles_x, int tiles_y,
+                                            int wave0, ChainRun& run, const DcChainArgs* ca, bool down = true) {
   using namespace dcw;
   constexpr int KH = KS;               // hidden k-steps per round (the pw2 k-steps of a round)
   constexpr int NT = 2 * KS + 2 * KH;  // weight-stream steps: pw1 rounds 0, 1, pw2
@@ -377,6 +362,7 @@ __device__ __forceinline__ void dc128_block(char* smem, const BlockArgs& a, int 
       load_row(8);
       dw_row(6);
       DW_WAIT(7, BAND_INSTR);
+      if constexpr (!LAST) chain_count_in(run, tile);
       load_row(9);
       dw_row(7);
 #undef DW_WAIT
@@ -431,29 +417,18 @@ __device__ __forceinline__ void dc128_block(char* smem, const BlockArgs& a, int 
             for (int q = 0; q < 2; ++q) res[c][g][q] = *(const half8*)(rb + 2 * g * BROW + ((f ^ (4 * c + 2 * q)) << 4));
       }
       // the ring, once every neighbouring tile has published block b - 1 (its
-      // edge pixels are in a.src): one lane of wave 0 per neighbour polls its
-      // word
-      if (wave == 0 && lane < 9 && lane != 4) {
-        const int ny = tyi + lane / 3 - 1, nx = txi + lane % 3 - 1;
-        if (ny >= 0 && ny < tiles_y && nx >= 0 && nx < tiles_x) {
-          const int* f = flags + ny * tiles_x + nx;
-          for (int spin = 0; __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < base + b; ++spin) {
-            if (spin > (1 << 16)) {  // about 0.1 s (a poll is a memory round trip): give up, record it
-              __hip_atomic_store(status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-          }
-        }
-      }
+      // edge pixels are in a.src)
+      if (wave == 0) chain_wait(run, b, lane, tyi, txi, tiles_y, tiles_x);
       lds_barrier();
       // the ring (52 pixels: rows -1 and 8, columns -1 and 16 of rows 0 .. 7)
       // through registers; the interior is this tile's previous output
       constexpr int RING = 2 * BW + 2 * TH;
-      half8 rv[(RING * 8 + 63) / 64];
-      int ro[(RING * 8 + 63) / 64];
+      constexpr int NR = (RING * 8 + 63) / 64;
+      half8 rv[NR];
+      const f16* rp[NR];
+      int ro[NR];
 #pragma unroll
-      for (int i = 0; i < (RING * 8 + 63) / 64; ++i) {
+      for (int i = 0; i < NR; ++i) {
         const int S = i * 64 + lane, r = S >> 3, u = S & 7;
         const int by = r < BW ? 0 : r < 2 * BW ? BH - 1 : 1 + (r - 2 * BW) % TH;
         const int bx = r < BW ? r : r < 2 * BW ? r - BW : (r < 2 * BW + TH ? 0 : BW - 1);
@@ -462,18 +437,12 @@ __device__ __forceinline__ void dc128_block(char* smem, const BlockArgs& a, int 
         // device-coherent loads (they bypass this XCD's L2, which may hold
         // an older copy of the line): the neighbours wrote these pixels in
         // this launch
-        rv[i] = load_coherent16(in ? z + (size_t)(hy * a.w + hx) * C + 64 * wave + 8 * u : zpad);
+        rp[i] = in ? z + (size_t)(hy * a.w + hx) * C + 64 * wave + 8 * u : zpad;
         ro[i] = S < RING * 8 ? by * BROW + bx * 128 + ((u ^ bswz(bx)) << 4) : -1;
       }
-      // the loads are opaque to the compiler: wait for them with the values
-      // as operands, so nothing reads them earlier
-      static_assert((RING * 8 + 63) / 64 == 7, "seven ring loads per lane");
-      asm volatile("s_waitcnt vmcnt(0)"
-                   : "+v"(rv[0]), "+v"(rv[1]), "+v"(rv[2]), "+v"(rv[3]), "+v"(rv[4]), "+v"(rv[5]), "+v"(rv[6])
-                   :
-                   : "memory");
+      load_coherent16(rv, rp);
 #pragma unroll
-      for (int i = 0; i < (RING * 8 + 63) / 64; ++i)
+      for (int i = 0; i < NR; ++i)
         if (ro[i] >= 0) *(half8*)(band + ro[i]) = rv[i];
       // pass 2: the outputs that read the ring, in the same order of taps
       load_row(0);
@@ -492,6 +461,7 @@ __device__ __forceinline__ void dc128_block(char* smem, const BlockArgs& a, int 
   // the bias loads of wave 0 (the band waits above cover them on a first block)
   if (!first) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   lds_barrier();  // a complete; every wave holds its residual, the bands are free
+  if constexpr (FIRST && !LAST) chain_tell(run, smem + SYNC);
 
   // ---- 2, 3. pw1 (steps 0 .. 31) and pw2 (steps 32 .. 63)
   floatx16 acc[2][4];  // pw1: chunk c, group g; pw2: output tile c, group g
@@ -614,6 +584,8 @@ __device__ __forceinline__ void dc128_block(char* smem, const BlockArgs& a, int 
   };
   unrolled(step, std::make_integer_sequence<int, NT>{});
 
+  bool late = false;
+  if constexpr (FIRST && !LAST) late = chain_too_late(run, smem + SYNC);
   lds_barrier();  // every wave is done reading the hidden layer
   if (last) {
     // ---- epilogue: one rounding to fp16, parked in LDS from offset 0 (row =
@@ -635,9 +607,9 @@ __device__ __forceinline__ void dc128_block(char* smem, const BlockArgs& a, int 
       }
     lds_barrier();
     if constexpr (CHAIN) {
-      if (ca->down_w) {
+      if (down && ca->down_w) {
         dc128_down(smem, *ca, a, ty0, tx0, wave, lane);
-        return;
+        return true;
       }
     }
     f16* dst = (f16*)a.dst;
@@ -685,6 +657,7 @@ __device__ __forceinline__ void dc128_block(char* smem, const BlockArgs& a, int 
         for (int u = 0; u < 8; ++u) *(half4*)(pb + ((u ^ sw) << 4)) = half4{};
       }
     }
+    if (FIRST && late) return false;
     // the tile's 44 edge pixels (rows 0 and 7, columns 0 and 15), the wave's
     // 64 channels, from the band to memory for the neighbours' rings
     f16* dst = (f16*)a.dst;
@@ -707,13 +680,13 @@ __device__ __forceinline__ void dc128_block(char* smem, const BlockArgs& a, int 
     // coherence (their acknowledgements counted down) before the tile's word
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();
-    if (threadIdx.x == 0) __hip_atomic_store(flags + tile, base + b + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    chain_publish(run, tile, b);
   }
+  return true;
 }
 
 template <bool CHAIN>
-__device__ __forceinline__ void dc128_body(const BlockArgs* blk, int nb, int* flags, int* status,
-                                           const DcChainArgs* ca) {
+__device__ __forceinline__ void dc128_body(const BlockArgs* blk, const DcChainArgs* ca) {
   using namespace dcw;
   __shared__ __attribute__((aligned(1024))) char smem[SMEM];
   const int tiles_x = (blk[0].w + TW - 1) / TW, tiles_y = (blk[0].h + TH - 1) / TH;
@@ -721,24 +694,37 @@ __device__ __forceinline__ void dc128_body(const BlockArgs* blk, int nb, int* fl
   if (tile >= tiles_x * tiles_y) return;
   const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if constexpr (!CHAIN) {
-    dc128_block<false, true, true>(smem, blk[0], 0, tile, tiles_x, tiles_y, wave0, 0, nullptr, nullptr, nullptr);
+    ChainRun none{};
+    dc128_block<false, true, true>(smem, blk[0], 0, tile, tiles_x, tiles_y, wave0, none, nullptr, false);
   } else {
     // nb >= 2: the first block, the middle ones, the last
-    const int base = __builtin_amdgcn_readfirstlane(__hip_atomic_load(flags + tile, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    dc128_block<true, true, false>(smem, blk[0], 0, tile, tiles_x, tiles_y, wave0, base, flags, status, ca);
-    for (int b = 1; b < nb - 1; ++b)
-      dc128_block<true, false, false>(smem, blk[b], b, tile, tiles_x, tiles_y, wave0, base, flags, status, ca);
-    dc128_block<true, false, true>(smem, blk[nb - 1], nb - 1, tile, tiles_x, tiles_y, wave0, base, flags, status,
-                                          ca);
+    const int nb = ca->nb;
+    ChainRun run = chain_begin(*ca, tile, tiles_x * tiles_y);
+    if (!dc128_block<true, true, false>(smem, blk[0], 0, tile, tiles_x, tiles_y, wave0, run, ca)) {
+      chain_end(run, tile);
+      return;
+    }
+    if (!chain_goes_on(run)) {
+      chain_sealed(run, nb, (uint32_t*)(smem + SYNC), [&](int b, int t) __attribute__((always_inline)) {
+        dc128_block<true, true, true>(smem, blk[b], 0, t, tiles_x, tiles_y, wave0, run, ca, b == nb - 1);
+      });
+      chain_end(run, tile);
+      return;
+    }
+    for (int i = 1; i < nb - 1; ++i) {
+      const int b = __builtin_amdgcn_readfirstlane(i);  // uniform for the compiler too: scalar loads of the arguments
+      dc128_block<true, false, false>(smem, blk[b], b, tile, tiles_x, tiles_y, wave0, run, ca);
+    }
+    dc128_block<true, false, true>(smem, blk[nb - 1], nb - 1, tile, tiles_x, tiles_y, wave0, run, ca);
   }
 }
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_dcblock128_f16(BlockArgs a) {
-  dc128_body<false>(&a, 1, nullptr, nullptr, nullptr);
+  dc128_body<false>(&a, nullptr);
 }
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_dcchain128_f16(DcChainArgs ca) {
-  dc128_body<true>(ca.blk, ca.nb, ca.flags, ca.status, &ca);
+  dc128_body<true>(ca.blk, &ca);
 }
 
 hipError_t launch_dcblock128_f16(const BlockArgs& a, hipStream_t st) {

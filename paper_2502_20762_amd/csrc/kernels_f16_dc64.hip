@@ -25,6 +25,7 @@
 #include <utility>
 
 #include "common.hpp"
+#include "dc_chain.hpp"
 #include "internal.hpp"
 
 namespace nc {
@@ -37,7 +38,7 @@ constexpr int BROW = BW * 128;             // bytes of a band row (64 channels)
 constexpr int XF = 1024 + 16;              // LDS stride of one B fragment
 constexpr int BAND_INSTR = (BH * BW * 8 + 63) / 64;  // 13 direct loads of 1 KiB per band
 constexpr int REG = BAND_INSTR * 1024;     // a 64-channel group's region: its band, later 8 fragments of a and 4 more
-static_assert(12 * XF <= REG, "twelve fragments per region");
+static_assert(12 * XF <= REG - 16 && BH * BW * 128 <= REG - 16, "twelve fragments per region, or a band, and the chains' word");
 
 // Position swizzle of the 16-byte units of band pixel (row y, column x): with
 // it the residual reads (16 lanes = two rows of 8 columns, one unit) and the
@@ -76,6 +77,7 @@ struct Geo {
   static constexpr int NX = C == 256 ? (GATED ? 0 : 16) : 2 * KH;
   static constexpr int OBIAS = OX + NX * XF;
   static constexpr int SMEM = OBIAS + 12 * C;
+  static constexpr int SYNC = REG - 16;  // a word no one else uses once the first band is in
   // registers per lane allow 2 workgroups per CU (4 at C = 64)
   static constexpr int WPE = C == 64 ? 4 : 2;
   static_assert(SMEM * WPE <= 160 * 1024, "WPE workgroups fit the LDS of a CU");
@@ -99,48 +101,6 @@ struct Geo {
 template <typename F, int... T>
 __device__ __forceinline__ void unrolled(F& f, std::integer_sequence<int, T...>) {
   (f(std::integral_constant<int, T>{}), ...);
-}
-
-// 16-byte device-coherent accesses (the sc1 policy of device-scope atomics:
-// past this XCD's L2 to the device's point of coherence), whole 128-byte lines
-// per 8 lanes, without a cache-wide fence (a fence would write back or drop
-// the whole L2, weights included).
-// N loads and the wait for them are one asm block, so nothing reads a result,
-// or reuses a register of it, while a load is in flight.
-template <int N>
-__device__ __forceinline__ void load_coherent16(half8 (&v)[N], const f16* const (&p)[N]) {
-  static_assert(N == 2 || N == 3 || N == 5, "ring loads per lane");
-  if constexpr (N == 2)
-    asm volatile(
-        "global_load_dwordx4 %0, %2, off sc1\n\t"
-        "global_load_dwordx4 %1, %3, off sc1\n\t"
-        "s_waitcnt vmcnt(0)"
-        : "=&v"(v[0]), "=&v"(v[1])
-        : "v"(p[0]), "v"(p[1])
-        : "memory");
-  else if constexpr (N == 3)
-    asm volatile(
-        "global_load_dwordx4 %0, %3, off sc1\n\t"
-        "global_load_dwordx4 %1, %4, off sc1\n\t"
-        "global_load_dwordx4 %2, %5, off sc1\n\t"
-        "s_waitcnt vmcnt(0)"
-        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2])
-        : "v"(p[0]), "v"(p[1]), "v"(p[2])
-        : "memory");
-  else
-    asm volatile(
-        "global_load_dwordx4 %0, %5, off sc1\n\t"
-        "global_load_dwordx4 %1, %6, off sc1\n\t"
-        "global_load_dwordx4 %2, %7, off sc1\n\t"
-        "global_load_dwordx4 %3, %8, off sc1\n\t"
-        "global_load_dwordx4 %4, %9, off sc1\n\t"
-        "s_waitcnt vmcnt(0)"
-        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4])
-        : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(p[4])
-        : "memory");
-}
-__device__ __forceinline__ void store_coherent16(f16* p, half8 v) {
-  asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
 }
 
 // The 2x2 stride-2 downsample of a tile's last block output (C = 256), which
@@ -203,11 +163,11 @@ __device__ __forceinline__ void dc64_down(const char* smem, const DcChainArgs& c
 }
 
 // One block of a tile (FIRST: its band comes whole from a.src; LAST: its
-// output goes whole to a.dst, or with ca->down_w set through the downsample to
-// ca->down_y; otherwise the chain's ring and edge exchange).
+// output goes whole to a.dst, or with ca->down_w set, and down, through the downsample
+// to ca->down_y; otherwise the chain's ring and edge exchange).
 template <int C, bool GATED, bool FIRST, bool LAST>
-__device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b, int tile, int tiles_x, int tiles_y,
-                                           int wave0, int base, int* flags, int* status, const DcChainArgs* ca) {
+__device__ __forceinline__ bool dc64_block(char* smem, const BlockArgs& a, int b, int tile, int tiles_x, int tiles_y,
+                                           int wave0, ChainRun& run, const DcChainArgs* ca, bool down = true) {
   using G = Geo<C, GATED>;
   constexpr int KS = G::KS, FR = G::FR, NT = G::NT, N1 = G::N1, KH = G::KH;
   const int tyi = tile / tiles_x, txi = tile - tyi * tiles_x;
@@ -442,6 +402,7 @@ __device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b
     };
     if constexpr (FIRST) {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      if constexpr (!LAST) chain_count_in(run, tile);
       lds_barrier();
       read_res();
       dw_rows();
@@ -461,21 +422,8 @@ __device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b
         }
       }
       // the ring, once every neighbouring tile has published block b - 1 (its
-      // edge pixels are in a.src): one lane of wave 0 per neighbour polls its
-      // word
-      if (wave == 0 && lane < 9 && lane != 4) {
-        const int ny = tyi + lane / 3 - 1, nx = txi + lane % 3 - 1;
-        if (ny >= 0 && ny < tiles_y && nx >= 0 && nx < tiles_x) {
-          const int* f = flags + ny * tiles_x + nx;
-          for (int spin = 0; __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < base + b; ++spin) {
-            if (spin > (1 << 16)) {  // about 0.1 s (a poll is a memory round trip): give up, record it
-              __hip_atomic_store(status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-          }
-        }
-      }
+      // edge pixels are in a.src)
+      if (wave == 0) chain_wait(run, b, lane, tyi, txi, tiles_y, tiles_x);
       lds_barrier();
       // the ring (36 pixels: rows -1 and 8, columns -1 and 8 of rows 0 .. 7)
       // through registers, split over the group's waves; device-coherent
@@ -547,6 +495,7 @@ __device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b
     }
   }
   lds_barrier();  // a and the biases complete; every wave holds its residual
+  if constexpr (FIRST && !LAST) chain_tell(run, smem + G::SYNC);
 
   // ---- 2, 3. pw1 and pw2
   floatx16 acc[2][2];
@@ -693,6 +642,8 @@ __device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b
   unrolled(step, std::make_integer_sequence<int, NT>{});
   if constexpr (C < 256) add_res();
 
+  bool late = false;
+  if constexpr (FIRST && !LAST) late = chain_too_late(run, smem + G::SYNC);
   lds_barrier();  // every wave is done reading the hidden layer
   // ---- the output, rounded to fp16 once, into the interior of the bands:
   // pixel (1 + y, 1 + x), 16-byte unit 4 (t % 2) + q, half h, of group t / 2;
@@ -719,10 +670,10 @@ __device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b
   lds_barrier();
   f16* dst = (f16*)a.dst;
   if constexpr (LAST) {
-    if constexpr (C == 256 && !FIRST) {
-      if (ca->down_w) {
+    if constexpr (C == 256) {
+      if (down && ca->down_w) {
         dc64_down(smem, *ca, a, ty0, tx0, wave, lane);
-        return;
+        return true;
       }
     }
     // whole pixels as 16-byte vectors
@@ -739,6 +690,7 @@ __device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b
       }
     }
   } else {
+    if (FIRST && late) return false;
     // the tile's 28 edge pixels, from the bands to memory for the neighbours' rings
     constexpr int EDGE = 2 * TW + 2 * (TH - 2);
     constexpr int NE = EDGE * (C / 8);
@@ -762,8 +714,9 @@ __device__ __forceinline__ void dc64_block(char* smem, const BlockArgs& a, int b
     // coherence (their acknowledgements counted down) before the tile's word
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();
-    if (threadIdx.x == 0) __hip_atomic_store(flags + tile, base + b + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    chain_publish(run, tile, b);
   }
+  return true;
 }
 
 // Workgroup -> tile: the first 256 workgroups (one per CU) take the first 256
@@ -787,7 +740,8 @@ void k_dcblock64_f16(BlockArgs a) {
   const int tile = dc64_tile();
   if (tile >= tiles_x * tiles_y) return;
   const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  dc64_block<C, GATED, true, true>(smem, a, 0, tile, tiles_x, tiles_y, wave0, 0, nullptr, nullptr, nullptr);
+  ChainRun none{};
+  dc64_block<C, GATED, true, true>(smem, a, 0, tile, tiles_x, tiles_y, wave0, none, nullptr, false);
 }
 
 // A chain: blocks 0 .. nb - 1 of a transform in one launch (blk[b] reads
@@ -795,12 +749,10 @@ void k_dcblock64_f16(BlockArgs a) {
 // of the next block's band, so between blocks only the ring of the band (the
 // neighbours' edge pixels) moves through memory: a block other than the last
 // stores only the tile's 28 edge pixels, then publishes its progress in
-// flags[tile]; the next block waits until every neighbouring tile has published
-// that block, then reads its ring.  Every tile of the grid must be resident at
-// once (the host checks the occupancy), and each wait gives up after a bounded
-// time, recording it in *status.  flags hold a running count: every launch
-// adds nb - 1 to each tile's word, so all words are equal between launches and
-// a launch reads its base from its own tile's word.
+// its word; the next block waits until every neighbouring tile has published
+// that block, then reads its ring.  The host launches a chain where the device holds
+// every tile of the grid at once; a launch that finds itself without room for them
+// all runs block by block with those that are there (chain_sync.hpp).
 template <int C, bool GATED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Geo<C, GATED>::WPE, Geo<C, GATED>::WPE)))
 void k_dcchain64_f16(DcChainArgs ca) {
@@ -810,13 +762,23 @@ void k_dcchain64_f16(DcChainArgs ca) {
   if (tile >= tiles_x * tiles_y) return;
   const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nb = ca.nb;
-  const int base =
-      __builtin_amdgcn_readfirstlane(__hip_atomic_load(ca.flags + tile, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-  dc64_block<C, GATED, true, false>(smem, ca.blk[0], 0, tile, tiles_x, tiles_y, wave0, base, ca.flags, ca.status, &ca);
-  for (int b = 1; b < nb - 1; ++b)
-    dc64_block<C, GATED, false, false>(smem, ca.blk[b], b, tile, tiles_x, tiles_y, wave0, base, ca.flags, ca.status, &ca);
-  dc64_block<C, GATED, false, true>(smem, ca.blk[nb - 1], nb - 1, tile, tiles_x, tiles_y, wave0, base, ca.flags,
-                                    ca.status, &ca);
+  ChainRun run = chain_begin(ca, tile, tiles_x * tiles_y);
+  if (!dc64_block<C, GATED, true, false>(smem, ca.blk[0], 0, tile, tiles_x, tiles_y, wave0, run, &ca)) {
+    chain_end(run, tile);
+    return;
+  }
+  if (!chain_goes_on(run)) {
+    chain_sealed(run, nb, (uint32_t*)(smem + Geo<C, GATED>::SYNC), [&](int b, int t) __attribute__((always_inline)) {
+      dc64_block<C, GATED, true, true>(smem, ca.blk[b], 0, t, tiles_x, tiles_y, wave0, run, &ca, b == nb - 1);
+    });
+    chain_end(run, tile);
+    return;
+  }
+  for (int i = 1; i < nb - 1; ++i) {
+    const int b = __builtin_amdgcn_readfirstlane(i);  // uniform for the compiler too: scalar loads of the arguments
+    dc64_block<C, GATED, false, false>(smem, ca.blk[b], b, tile, tiles_x, tiles_y, wave0, run, &ca);
+  }
+  dc64_block<C, GATED, false, true>(smem, ca.blk[nb - 1], nb - 1, tile, tiles_x, tiles_y, wave0, run, &ca);
 }
 
 template <int C>
