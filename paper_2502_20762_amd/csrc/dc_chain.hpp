@@ -186,10 +186,13 @@ __device__ __forceinline__ void load_coherent16(V (&v)[N], const T* const (&p)[N
         : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(p[4]), "v"(p[5]), "v"(p[6])
         : "memory");
 }
+// A store of more than 8 bytes still reads its data registers when the next instructions issue:
+// two wait states must lie before a VALU instruction may write them.  The compiler keeps that
+// distance for its own stores but does not see into this one.
 template <typename V, typename T>
 __device__ __forceinline__ void store_coherent16(T* p, V v) {
   static_assert(sizeof(V) == 16, "16 bytes");
-  asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
 
 }  // namespace nc

@@ -355,7 +355,8 @@ __device__ __forceinline__ bool dc64_block(char* smem, const BlockArgs& a, int b
       } else {
         // even rows, odd columns: the last tap's sum is rounded to fp16 by the fma itself, at
         // the others to fp32 and then to fp16 (fixed here, so that it does not depend on the
-        // compiler's choice of instructions)
+        // compiler's choice of instructions; a wait state lies between a half-register result and
+        // its reader)
         const bool fused = r % 2 == 0 && k % 2 == 1;
 #pragma unroll
         for (int t = 0; t < (fused ? 8 : 9); ++t) {
@@ -364,8 +365,8 @@ __device__ __forceinline__ bool dc64_block(char* smem, const BlockArgs& a, int b
           a1 = fmaf((float)ww[1], (float)zz[1], a1);
         }
         if (fused) {
-          asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,1,0]\n\t"
-              "v_fma_mixhi_f16 %0, %1, %2, %4 op_sel:[1,1,0] op_sel_hi:[1,1,0]"
+          asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,1,0]\n\ts_nop 0\n\t"
+              "v_fma_mixhi_f16 %0, %1, %2, %4 op_sel:[1,1,0] op_sel_hi:[1,1,0]\n\ts_nop 0"
               : "=&v"(out[r][k])
               : "v"(wt[8]), "v"(V[r + 2][k + 2]), "v"(a0), "v"(a1));
           return;
