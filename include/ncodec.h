@@ -371,11 +371,13 @@ ncodec_status ncodec_graph_enable(ncodec_ctx* ctx, int32_t enable);
  * 8 x 8 or 255 of 8 x 16 at 1080p), on the fp16 path below C = 256 up to 256
  * tiles; otherwise, and with enable = 0, one launch per block.  Results are
  * identical either way, also where a launch finds part of the device taken
- * by another stream's kernel or another process: its workgroups wait a few
- * milliseconds for the rest, then those that are there run the blocks one after
+ * by another stream's kernel or another process: its workgroups wait about
+ * 1.5 ms for the rest, then those that are there run the blocks one after
  * the other (a slow launch, the same results).  On by default.  Chains of
- * different streams of a process are ordered one after the other unless they are
- * small (at most 64 tiles each).
+ * different streams of a process run beside each other while their tiles fit the device
+ * together; a further one is ordered after the oldest of them (after
+ * that chain, not after what else its stream holds).  Chains that a caller captures into a
+ * graph of its own are replayed in no such order.
  * enable = NCODEC_CHAINS_SEALED: every chain launch takes the way of one without
  * room for its tiles (for tests of it).
  * Changing the setting drops captured graphs (the next graph call captures
@@ -387,7 +389,8 @@ ncodec_status ncodec_block_chains(ncodec_ctx* ctx, int32_t enable);
  * and size that have them, and where the shortest chain is four blocks, a run that
  * long), else 0.  Synchronizes the
  * context's stream and writes to *timeouts 1 if any chain launch of this
- * context has given up waiting for a neighbouring tile since its creation,
+ * context has given up waiting for a neighbouring tile since its creation
+ * (all tiles of a chain that waits are on the device, so that is not expected),
  * else 0.  Errors: EINVAL for a NULL ctx, in_use or timeouts, EHIP. */
 ncodec_status ncodec_block_chain_status(ncodec_ctx* ctx, int32_t* in_use, int32_t* timeouts);
 

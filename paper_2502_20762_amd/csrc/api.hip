@@ -8,12 +8,12 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <mutex>
 #include <string>
 #include <type_traits>
 #include <vector>
 
 #include "../../include/ncodec.h"
+#include "chain_gate.hpp"
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -777,6 +777,7 @@ struct ncodec_ctx {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<CapturedNode> nodes;
+    bool chains = false;  // the graph holds a chain launch
     const void* ptr[3] = {nullptr, nullptr, nullptr};
   };
   bool use_graphs = false;
@@ -785,6 +786,7 @@ struct ncodec_ctx {
   // at once; chain_fit: -1 not yet checked, 0 no, 1 yes)
   bool chains = true, seal_chains = false;  // seal_chains: NCODEC_CHAINS_SEALED
   int chain_fit = -1;
+  int cus = 0;  // of the device
   // Parallel coding (Fig. 6; supplementary "Parallel Coding"): the coded
   // calls run the entropy coder (encode) or the feature extractor (decode) on
   // a second stream of default priority, joined by events before the call's
@@ -792,9 +794,9 @@ struct ncodec_ctx {
   bool overlap = false;
   hipStream_t aux = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-  hipEvent_t ev_gate = nullptr;  // orders this context's chains after other streams'
   hipStream_t cap_stream = nullptr;
   std::vector<CapturedNode>* capturing = nullptr;
+  bool captured_chain = false;  // a chain was launched into the capture
   bool is_int() const { return cfg.path == NCODEC_PATH_INT16; }
   template <class T = void> T* p(size_t off) const { return (T*)(ws + off); }
 };
@@ -963,73 +965,42 @@ int next_launch(ncodec_ctx* ctx, int n) {
   return m >= shortest_chain(ctx) && chains_usable(ctx) ? m : 1;
 }
 
-// Chains on one device.  A chain's workgroups wait for each other, so two
-// chains that each hold part of the device and need the rest would wait until
-// both give up.  Within a process that is ruled out here: a chain launch on a
-// stream is ordered after the chains in flight on other streams, unless all of
-// them are small (at most a quarter of the CUs, so that the four hardware
-// queues' worth of them fit together).  Entries are per stream, added by the
-// launching context and removed when it is destroyed.
-struct ChainGate {
-  struct Entry {
-    const ncodec_ctx* ctx;
-    hipStream_t stream;
-    bool small;
-  };
-  std::mutex m;
-  std::vector<Entry> active;
+struct GateOps {
+  using Stream = hipStream_t;
+  using Event = hipEvent_t;
+  static void wait(Stream s, Event e) { clear(hipStreamWaitEvent(s, e, 0)); }
+  static bool record(Event& e, Stream s) {
+    if (!e && !clear(hipEventCreateWithFlags(&e, hipEventDisableTiming))) return false;
+    return clear(hipEventRecord(e, s));
+  }
+  static void destroy(Event e) {
+    if (e) (void)hipEventDestroy(e);
+  }
+  // an error here is no call's result, and not the next launch's either
+  static bool clear(hipError_t e) {
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e == hipSuccess;
+  }
 };
 constexpr int kMaxDevices = 64;
-ChainGate g_gates[kMaxDevices];
+ChainGate<GateOps> g_gates[kMaxDevices];
 
-bool capturing(hipStream_t st) {
+// Launches a chain (or a graph that holds one) on ctx->stream, in the order of the device's
+// chains.  On a stream that the caller captures there is none: nothing can be ordered across the
+// edge of a capture, and the launch is the replay's.
+template <class F>
+hipError_t launch_chained(ncodec_ctx* ctx, F&& launch) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
-}
-
-// Called before a chain (or a graph that holds one) is launched on ctx->stream.
-hipError_t gate_chain(ncodec_ctx* ctx) {
-  if (ctx->device < 0 || ctx->device >= kMaxDevices) return hipSuccess;
-  ChainGate& g = g_gates[ctx->device];
-  const hipStream_t st = ctx->stream;
-  const bool small = dc_tiles(ctx) <= 64;
-  std::lock_guard<std::mutex> lock(g.m);
-  bool own = false;
-  for (size_t i = 0; i < g.active.size();) {
-    ChainGate::Entry& e = g.active[i];
-    if (e.stream == st) {
-      own = true;
-      e.small = e.small && small;
-      ++i;
-      continue;
-    }
-    // nothing can be ordered across the edge of a capture
-    if ((small && e.small) || capturing(st) || capturing(e.stream)) {
-      ++i;
-      continue;
-    }
-    if (!ctx->ev_gate) {
-      const hipError_t err = hipEventCreateWithFlags(&ctx->ev_gate, hipEventDisableTiming);
-      if (err != hipSuccess) return err;
-    }
-    hipError_t err = hipEventRecord(ctx->ev_gate, e.stream);
-    if (err == hipSuccess) err = hipStreamWaitEvent(st, ctx->ev_gate, 0);
-    if (err != hipSuccess) return err;
-    // a later launch that must wait for e waits for this one if this is not small
-    if (small) ++i;
-    else g.active.erase(g.active.begin() + i);
-  }
-  if (!own) g.active.push_back({ctx, st, small});
-  return hipSuccess;
+  if (ctx->device < 0 || ctx->device >= kMaxDevices || ctx->capturing ||
+      !GateOps::clear(hipStreamIsCapturing(ctx->stream, &cs)) || cs != hipStreamCaptureStatusNone)
+    return launch();
+  // in halves of a CU: a tile of 8 x 8 needs one, of 8 x 16 the whole
+  const int share = dc_tiles(ctx) * (dc_tile64(ctx) ? 1 : 2);
+  return g_gates[ctx->device].launch(ctx, ctx->stream, share, 2 * ctx->cus, std::forward<F>(launch));
 }
 
 void leave_gate(const ncodec_ctx* ctx) {
-  if (ctx->device < 0 || ctx->device >= kMaxDevices) return;
-  ChainGate& g = g_gates[ctx->device];
-  std::lock_guard<std::mutex> lock(g.m);
-  for (size_t i = 0; i < g.active.size();)
-    if (g.active[i].ctx == ctx) g.active.erase(g.active.begin() + i);
-    else ++i;
+  if (ctx->device >= 0 && ctx->device < kMaxDevices) g_gates[ctx->device].leave(ctx);
 }
 
 // One DC block of either form, src -> dst.
@@ -1111,15 +1082,16 @@ hipError_t run_blocks(ncodec_ctx* ctx, const std::vector<BlockDev>& blocks, cons
       ca.down_y = down_y;
       *down_done = true;
     }
-    hipError_t e = ctx->capturing ? hipSuccess : gate_chain(ctx);
-    if (e != hipSuccess) return e;
-    e = timed(ctx, fuse ? "dcblock_down" : "dcblock", [&] {
-      const int C = ctx->cfg.channels;
-      if (dc_tile64(ctx))
-        return ctx->is_int() ? launch_dcchain64_i16(C, gated, ca, ctx->stream)
-                             : launch_dcchain64_f16(C, gated, ca, ctx->stream);
-      return launch_dcchain128_f16(ca, ctx->stream);
-    }, m);
+    if (ctx->capturing) ctx->captured_chain = true;
+    const hipError_t e = launch_chained(ctx, [&] {
+      return timed(ctx, fuse ? "dcblock_down" : "dcblock", [&] {
+        const int C = ctx->cfg.channels;
+        if (dc_tile64(ctx))
+          return ctx->is_int() ? launch_dcchain64_i16(C, gated, ca, ctx->stream)
+                               : launch_dcchain64_f16(C, gated, ca, ctx->stream);
+        return launch_dcchain128_f16(ca, ctx->stream);
+      }, m);
+    });
     if (e != hipSuccess) return e;
     k0 += m;
   }
@@ -1581,6 +1553,7 @@ ncodec_status run_graph(ncodec_ctx* ctx, bool decode, const void* p0, const void
     ctx->stream = ctx->cap_stream;
     gs.nodes.clear();
     ctx->capturing = &gs.nodes;
+    ctx->captured_chain = false;
     hipError_t e = hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal);
     ncodec_status st = NCODEC_OK;
     if (e == hipSuccess) {
@@ -1604,12 +1577,13 @@ ncodec_status run_graph(ncodec_ctx* ctx, bool decode, const void* p0, const void
       gs = ncodec_ctx::GraphSlot{};
       return st;
     }
+    gs.chains = ctx->captured_chain;
     for (int i = 0; i < 3; ++i) gs.ptr[i] = ptr[i];
   } else {
     NC_HIP(ctx, retarget(ctx, gs, decode, ptr), "graph update");
   }
-  if (chains_usable(ctx)) NC_HIP(ctx, gate_chain(ctx), "graph launch");
-  NC_HIP(ctx, hipGraphLaunch(gs.exec, ctx->stream), "graph launch");
+  auto replay = [&] { return hipGraphLaunch(gs.exec, ctx->stream); };
+  NC_HIP(ctx, gs.chains ? launch_chained(ctx, replay) : replay(), "graph launch");
   return NCODEC_OK;
 }
 
@@ -1668,6 +1642,7 @@ ncodec_status ncodec_create(const ncodec_config* cfg, const float* host_weights,
   ctx->ws = (char*)d_workspace;
   ctx->L = std::move(L);
   hipError_t e = hipGetDevice(&ctx->device);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&ctx->cus, hipDeviceAttributeMultiprocessorCount, ctx->device);
   if (e == hipSuccess) e = hipMemcpyAsync(ctx->ws, img.bytes.data(), img.bytes.size(), hipMemcpyHostToDevice, ctx->stream);
   if (e == hipSuccess) e = launch_fill_zero(ctx->ws + ctx->L.image_bytes, ctx->L.total - ctx->L.image_bytes, nullptr, 0, ctx->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
@@ -2138,6 +2113,7 @@ void ncodec_destroy(ncodec_ctx* ctx) {
   if (!ctx) return;
   (void)hipSetDevice(ctx->device);
   (void)hipStreamSynchronize(ctx->stream);
+  if (ctx->aux) (void)hipStreamSynchronize(ctx->aux);
   leave_gate(ctx);
   for (auto& t : ctx->log) {
     if (t.start) (void)hipEventDestroy(t.start);
@@ -2149,11 +2125,7 @@ void ncodec_destroy(ncodec_ctx* ctx) {
       if (gs.graph) (void)hipGraphDestroy(gs.graph);
     }
   if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
-  if (ctx->aux) {
-    (void)hipStreamSynchronize(ctx->aux);
-    (void)hipStreamDestroy(ctx->aux);
-  }
-  if (ctx->ev_gate) (void)hipEventDestroy(ctx->ev_gate);
+  if (ctx->aux) (void)hipStreamDestroy(ctx->aux);
   if (ctx->ev_fork) (void)hipEventDestroy(ctx->ev_fork);
   if (ctx->ev_join) (void)hipEventDestroy(ctx->ev_join);
   delete ctx;

@@ -26,8 +26,8 @@ struct DevMem {
 
 // Polls are memory round trips, about 1.5 us: a neighbour's block and the barriers of a sealed
 // launch may take a second (every workgroup waited for is running), the rest of the launch is
-// waited for about 6 ms.
-constexpr int kChainWait = 1 << 16, kChainMeet = 1 << 20, kChainRest = 1 << 12;
+// waited for about 1.5 ms, longer than the launches of a codec that may hold its places.
+constexpr int kChainWait = 1 << 16, kChainMeet = 1 << 20, kChainRest = 1 << 10;
 
 // What a workgroup of a chain launch knows of it.
 struct ChainRun {

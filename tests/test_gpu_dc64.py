@@ -3,7 +3,7 @@ run the same per-block arithmetic (q, bits, state and decoded frame must agree b
 wait may time out), for every width and form, at sizes with one tile, whole tiles, tiles cut at
 the right and bottom, more tiles than CUs, and both sides of the rule between 8 x 8 and 8 x 16
 tiles (fp16, C = 256).  The blocks themselves are checked against the oracle by the parity
-tests of every width.  Then chains of two contexts on two streams, enqueued from two threads at once."""
+tests of every width.  Then two contexts on two streams, enqueued from two threads at once."""
 import threading
 
 import numpy as np
@@ -102,14 +102,20 @@ def test_int_blocks_saturate_like_the_oracle(C, block, H, W):
     np.testing.assert_array_equal(host(enc.get_state()[0]).astype(np.int64), r.state.feat)
 
 
-def test_chains_on_two_streams():
-    # each context's chain needs most of the device; enqueued from two threads
-    # on two streams they must not wait for each other
-    sizes = [(480, 832, 128), (1088, 1920, 256)]
-    frames = {s: [torch.from_numpy(synth.random_frame(s[0], s[1], seed=70 + t)).to(DEV) for t in range(2)] for s in sizes}
+@pytest.mark.parametrize("specs,graphs", [
+    ([("fp16", 480, 832, 128), ("fp16", 1088, 1920, 256)], False),  # 104 tiles of 8 x 8, 255 of 8 x 16
+    ([("int16", 1088, 1920, 256), ("fp16", 1088, 1920, 256)], False),  # 510 and 255: each most of the device
+    ([("int16", 1088, 1920, 256), ("fp16", 1088, 1920, 256)], True),
+])
+def test_chains_on_two_streams(specs, graphs):
+    # an ordinary parity check: two contexts, enqueued from two threads on two streams, give what each gives
+    # alone and no wait gives up (which launch waits for which is checked on the host)
+    frames = {s: [torch.from_numpy(synth.random_frame(s[1], s[2], seed=70 + t)).to(DEV) for t in range(2)] for s in specs}
 
     def codec(s, stream):
-        return Codec(s[0], s[1], s[2], 4, 4, "fp16", synth.make_weights(s[2], 4, 4), device=DEV, stream=stream)
+        c = Codec(s[1], s[2], s[3], 4, 4, s[0], synth.make_weights(s[3], 4, 4), device=DEV, stream=stream)
+        c.graphs(graphs)
+        return c
 
     def loop(c, s, n):
         out = []
@@ -120,25 +126,25 @@ def test_chains_on_two_streams():
         return out
 
     want = {}
-    for s in sizes:
+    for s in specs:
         c = codec(s, None)
         want[s] = [(host(q), host(b)) for q, b in loop(c, s, 12)]
         c.close()
     torch.cuda.synchronize()
-    codecs = [codec(s, torch.cuda.Stream()) for s in sizes]
+    codecs = [codec(s, torch.cuda.Stream()) for s in specs]
     torch.cuda.synchronize()
     got = {}
 
     def work(c, s):
         got[s] = loop(c, s, 12)
 
-    threads = [threading.Thread(target=work, args=(c, s)) for c, s in zip(codecs, sizes)]
+    threads = [threading.Thread(target=work, args=(c, s)) for c, s in zip(codecs, specs)]
     for t in threads:
         t.start()
     for t in threads:
         t.join()
     torch.cuda.synchronize()
-    for c, s in zip(codecs, sizes):
+    for c, s in zip(codecs, specs):
         assert c.block_chain_status() == (1, 0)
         for t, ((q, b), (qw, bw)) in enumerate(zip(got[s], want[s])):
             np.testing.assert_array_equal(host(q), qw, err_msg=f"{s} frame {t}: q")
