@@ -100,7 +100,8 @@ def test_chain_modules_and_graphs_match_per_block_launches(path):
 
 
 def test_int_gated_runs_without_chains():
-    # the int16 gated block keeps one launch per block: chains report not in use
+    # runs of two int16 gated blocks keep one launch per block (its shortest chain is four): chains report
+    # not in use
     frames = [synth.random_frame(64, 96, seed=35)]
     flat = synth.make_weights(256, 2, 2, block="gated")
     c = Codec(64, 96, 256, 2, 2, "int16", flat, device=DEV, block="gated")
