@@ -135,11 +135,22 @@ static hipError_t launch_dw3x3(const void* src, const void* dww, void* dst, int 
     const int64_t n = ((int64_t)((h + rows - 1) / rows) * ((w + cols - 1) / cols) * (C / 8) + 255) / 256;
     return dim3((unsigned)((n + 7) / 8 * 8));
   };
-  // strips of 8 x 2 while they still give every SIMD a wave, else of 2 x 1
+  // Strips of 8 x 2 while they still give every SIMD a wave (256 workgroups), of 2 x 1 while
+  // these give more than 1.5 workgroups per CU, else single pixels.  us per decode with four
+  // blocks, fp16 then int16:
+  //   2 x 1 / 8 x 2 (workgroups of 8 x 2): 832 x 480 C = 512 (104) 178 / 190, 280 / 287; 720p C
+  //     = 384 (184) 222 / 224, 391 / 388; C = 512 (240) 299 / 290, 539 / 522; 1080p C = 384
+  //     (384) 388 / 361, 707 / 669; C = 512 (512) 553 / 498, 1103 / 1044
+  //   1 x 1 / 2 x 1 (workgroups of 2 x 1), C = 512: 64 x 64 (8) 111 / 115, 184 / 188; 256 x 256
+  //     (128) 115 / 118, 191 / 193; 320 x 480 (304) 127.5 / 130.5, 205.4 / 206.7; 384 x 512
+  //     (384) 128.5 / 129.4, 203.9 / 204.1; 384 x 640 (480) 137.4 / 135.2, 212.6 / 208.0; 832 x
+  //     480 (784) 178 / 175, 281 / 279
   if ((int64_t)grid(8, 2).x * 4 >= 1024)
     launch(k_dw3x3<IS_INT, 8, 2>, grid(8, 2), dim3(256), st, src, (const uint32_t*)dww, dst, C, h, w);
-  else
+  else if (grid(2, 1).x > 384)
     launch(k_dw3x3<IS_INT, 2, 1>, grid(2, 1), dim3(256), st, src, (const uint32_t*)dww, dst, C, h, w);
+  else
+    launch(k_dw3x3<IS_INT, 1, 1>, grid(1, 1), dim3(256), st, src, (const uint32_t*)dww, dst, C, h, w);
   return hipGetLastError();
 }
 

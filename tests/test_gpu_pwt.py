@@ -82,8 +82,11 @@ def variants(H, W, C, block):
     if C > 256:
         pick("gate" if block == "gated" else "lrelu", 2 * C, p8)
         pick("resid", C, p8)
-        n = -(-(-(-(H // 8) // 8) * -(-(W // 8) // 2) * (C // 8)) // 256)
-        out.append(("dw", 8 if -(-n // 8) * 8 >= 256 else 2))
+        def dw(rows, cols):
+            n = -(-(-(-(H // 8) // rows) * -(-(W // 8) // cols) * (C // 8)) // 256)
+            return -(-n // 8) * 8
+
+        out.append(("dw", 8 if dw(8, 2) >= 256 else 2 if dw(2, 1) > 384 else 1))
     return set(out)
 
 
@@ -91,7 +94,7 @@ def test_sizes_reach_every_variant():
     got = set().union(*(variants(*s) for s in SIZES))
     want = {(l, *t) for l, ts in {"rec": ((2, 4), (2, 2), (1, 2)), "embed": ((2, 4), (1, 4), (1, 2)), "up": ((2, 4), (1, 2)),
                                   "lrelu": ((2, 4), (1, 4), (1, 2)), "resid": ((2, 4), (1, 4), (1, 2)),
-                                  "gate": ((2, 4), (2, 2))}.items() for t in ts} | {("dw", 8), ("dw", 2)}
+                                  "gate": ((2, 4), (2, 2))}.items() for t in ts} | {("dw", r) for r in (8, 2, 1)}
     assert got == want, (want - got, got - want)
 
 
@@ -142,12 +145,16 @@ def test_frame_against_the_oracle(H, W, C, block):
             close(yh[l], after.yhat, "yhat")
 
 
-@pytest.mark.parametrize("block", ["lrelu", "gated"])
-def test_wide_depthwise_strips_int_bit_exact(block):
-    # strips of 8 x 2 on 134 x 186 pixels: cut at the bottom (134 = 16 * 8 + 6); the smaller sizes of the
-    # wide tests take the strips of 2 x 1
-    H, W, C = 1072, 1488, 512
-    assert ("dw", 8) in variants(H, W, C, block)
+@pytest.mark.parametrize("rows,H,W,block", [
+    (8, 1072, 1488, "lrelu"),  # strips of 8 x 2 on 134 x 186 pixels: cut at the bottom (134 = 16 * 8 + 6)
+    (8, 1072, 1488, "gated"),
+    (2, 368, 656, "lrelu"),    # of 2 x 1 on 46 x 82
+    (1, 384, 512, "lrelu"),    # the largest launch of single pixels
+    (1, 48, 80, "gated"),
+])
+def test_wide_depthwise_strips_int_bit_exact(rows, H, W, block):
+    C = 512
+    assert ("dw", rows) in variants(H, W, C, block)
     flat = synth.make_weights(C, 1, 1, block=block)
     p = oracle.unpack(flat, C, 1, 1, block=block)
     ip = ci.integerize(p)
