@@ -106,10 +106,11 @@ def cpu_baseline(pre, weights, strip_rows, path="fp16"):
 
 TRAFFIC_PROFILE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles", "dcblock_hd1080_hbm_traffic.md")
 CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2502_20762_amd", "csrc")
-SOURCES = {"k_dcchain128_f16": ["kernels_f16_dc128.hip", "common.hpp", "internal.hpp"],
-           "k_dcblock128_f16": ["kernels_f16_dc128.hip", "common.hpp", "internal.hpp"],
-           "k_dcchain64_i16<256,false>": ["kernels_i16_dc64.hip", "common.hpp", "internal.hpp"],
-           "k_dcblock64_i16<256,false>": ["kernels_i16_dc64.hip", "common.hpp", "internal.hpp"]}
+DC_HEADERS = ["dc_chain.hpp", "chain_sync.hpp", "common.hpp", "internal.hpp"]
+SOURCES = {"k_dcchain128_f16": ["kernels_f16_dc128.hip", *DC_HEADERS],
+           "k_dcblock128_f16": ["kernels_f16_dc128.hip", *DC_HEADERS],
+           "k_dcchain64_i16<256,false>": ["kernels_i16_dc64.hip", *DC_HEADERS],
+           "k_dcblock64_i16<256,false>": ["kernels_i16_dc64.hip", *DC_HEADERS]}
 
 
 def counted_traffic(kernel):

@@ -917,11 +917,16 @@ PwArgs conv_args(const ncodec_ctx* ctx, const ConvDev& c, int K, int N, int P) {
 // run as a chain of 8 x 16 ones.  Up to 256 tiles of 8 x 8 each has a CU of its own; with
 // two per CU one's VALU and memory phases run beside the other's MFMA loops, but every
 // tile streams the whole block's weights from L2, which the larger tile halves.  us per
-// chained fp16 block at C = 256, 8 x 8 / 8 x 16: 720p gated (240 tiles) 13.4 / 21.2,
-// LeakyReLU 896 x 1280 (280) 18.1 / 19.3, 1024 x 1280 (320) 19.1 / 19.4, 1024 x 1536 (384)
-// 20.0 / 19.9, 1088 x 1664 (442) 21.9 / 20.9, 1080p (510) 22.2 / 21.9, 1080p gated 21.6 /
-// 22.7; one launch per block at 4K 84.8 / 91.7.  Integer blocks (twice the MFMAs per weight
-// byte, more VALU work): 1080p 33.7 / 38, 720p 22.5 / 36, 4K 129 / 153.
+// chained fp16 LeakyReLU block at C = 256, 8 x 8 / 8 x 16: 720p (240 tiles) 12.2 /
+// 18.6, 896 x 1280 (280) 17.3 / 18.6, 1024 x 1280 (320) 17.9 / 18.7, 1024 x 1536 (384) 19.2 /
+// 18.8, 1088 x 1664 (442) 20.9 / 19.6, 1080p (510) 22.6 / 20.5; one launch per block at 4K
+// 84.9 / 87.8.  Gated blocks cannot tell the two apart at 1080p (us per encode 404 / 391, 431 /
+// 438, 435 / 435, 422 / 426 on four cards, per decode 194 / 199, 197 / 199, 201 / 200 on three)
+// and take 8 x 8 up to there (1024 x 1536 encode 372 / 395, 1088 x 1664 400 / 412).  The
+// downsample is fused on either (8 x 8, gated 1080p encode, fused / its own launch 404.5 / 407.7,
+// 720p 236.9 / 241.5).
+// Integer blocks (twice the MFMAs per weight byte, more VALU work): 1080p 33.7 / 38, 720p 22.5
+// / 36, 4K 129 / 153.
 bool dc_tile64(const ncodec_ctx* ctx) {
   const int h8 = ctx->cfg.height / 8, w8 = ctx->cfg.width / 8;
   if (ctx->is_int() || ctx->cfg.channels < 256 || ctx->cfg.block == NCODEC_BLOCK_GATED) return true;
@@ -955,8 +960,12 @@ bool chains_usable(ncodec_ctx* ctx) {
 
 // Blocks of the next launch of a run with n blocks left: a chain of up to
 // kMaxChain, or one.  The shortest chain is two blocks at C = 256, but four for
-// the small models and the integer gated form (ncodec_kernels_per_frame and
-// ncodec_block_chain_status promise one launch per block for their shorter runs).
+// the small models and the integer gated form, whose short chains cost about what the
+// launches do (ncodec_kernels_per_frame and ncodec_block_chain_status state that too).  us
+// per decode of two blocks, one launch each / chained: 832 x 480 C = 128 int16 41.0 / 43.0, fp16
+// 31.2 / 29.4, 64 x 64 C = 64 int16 26.8 / 30, fp16 22.1 / 21.7, 992 x 544 int16 gated C = 128
+// 44.6 / 45.4, C = 256 78.1 / 81.0; of three: 50.9 / 50.1, 35.1 / 34.8, 32.5 / 34.3, 22 / 21.4,
+// 55.3 / 54.1, 98.9 / 103.8.
 int shortest_chain(const ncodec_ctx* ctx) {
   return ctx->cfg.channels == 256 && !(ctx->is_int() && ctx->cfg.block == NCODEC_BLOCK_GATED) ? 2 : 4;
 }

@@ -1,4 +1,5 @@
-// fp16 DC block (Supp. B.1, LeakyReLU form) for C = 256 with 128 pixels per wave: each wave covers the whole 8 x 16 pixel tile of its workgroup, so
+// fp16 DC block (Supp. B.1, LeakyReLU form) for C = 256 with 128 pixels per
+// wave: each wave covers the whole 8 x 16 pixel tile of its workgroup, so
 // every weight fragment it loads feeds four MFMAs (the tile's four 32-pixel
 // groups).  The weight fragments are therefore read straight from global
 // memory (L2) into registers as MFMA A operands, never staged through LDS;

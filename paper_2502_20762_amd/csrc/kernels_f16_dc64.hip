@@ -9,17 +9,20 @@
 //      them); each group's halo band (10 x 10 pixels, 128 bytes per pixel)
 //      lies in a region of its own.  256 / C waves share a group, each
 //      filtering its rows; lane = (channel pair, column half), accumulated in
-//      fp32 from the bias with v_dot2_f32_f16, rounded to fp16 once and kept
-//      in registers until the band has been read (the residual of the
+//      fp32 from the bias (C = 256: v_dot2_f32_f16, below it an fma per tap),
+//      rounded to fp16 once and kept in registers until the band has been read (the residual of the
 //      wave's outputs, the band's interior, goes to registers too), then
 //      written over the band as B fragments of a.
 //   2. pw1.  The 2C hidden channels are chunks of 32; the waves run the chains
-//      of their chunks over both pixel groups, LeakyReLU (or the gate) on the
-//      fp16-rounded value, and write the result as pw2 B fragments.  C = 256
-//      takes two rounds (the second writes over a).
-//   3. pw2.  Each wave accumulates its 32-row output tiles from the bias plus
-//      the residual (identity MFMAs, exact products) over the hidden layer;
-//      the sums are rounded to fp16 once.
+//      of their chunks over both pixel groups, the LeakyReLU (C = 256: on the
+//      fp16-rounded value, below it in fp32) or the gate, and write the result
+//      as pw2 B fragments.  C = 256 takes two rounds (the second writes over a).
+//   3. pw2.  Each wave accumulates its 32-row output tiles from the bias over
+//      the hidden layer; the residual enters through identity MFMAs (exact
+//      products), at C = 256 before the hidden layer, below it after; the
+//      sums are rounded to fp16 once.
+// Where C = 256 and the smaller widths differ, each has the order and the roundings that its
+// frames have always had, so that a stream does not depend on the kernel that coded it.
 // Every weight fragment is read straight from global memory (L2) as an MFMA A
 // operand and feeds both pixel groups.
 #include <utility>
@@ -726,8 +729,8 @@ __device__ __forceinline__ bool dc64_block(char* smem, const BlockArgs& a, int b
 // then run half a block out of step, one in its MFMA loops while the other is
 // in its VALU and memory phases.  (Left to themselves the first of the two, the older,
 // always goes first; the frame's second half then falls two blocks behind and
-// its neighbours wait: with the lead alternating from block to block a chained integer
-// block at 1080p takes 37.9 us instead of 39.3, gated 34.5 instead of 36.9.)
+// its neighbours wait.  With the lead alternating from block to block a gated 1080p encode
+// takes 435 us instead of 451, a decode 196.6 instead of 197.2.)
 __device__ __forceinline__ int dc64_tile() {
   const int slot = blockIdx.x >> 8, n = min(256, (int)gridDim.x - (slot << 8));
   return (slot << 8) + xcd_tile(blockIdx.x & 255, n);

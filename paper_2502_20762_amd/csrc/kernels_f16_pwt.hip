@@ -280,7 +280,7 @@ int wgs(const PwArgs& a, int rt, int pg) { return (a.P + 32 * pg - 1) / (32 * pg
 // with 256 x 64 in the middle: K = 256 1080p 9.8 us against 12.8 with 128 x 64, 720p 7.2
 // / 6.8, 832 x 480 6.6 / 5.6; K = 512 1080p 13.4 / 15.6.
 // At 1080p, C = 512 the halves took 58 and 54 us with both operands staged through LDS,
-// 39 and 40 us here (870 TFLOP/s; the same box).
+// 39 and 40 us here (870 TFLOP/s; the same card).
 template <int LOADER, int EPI>
 hipError_t pick(const PwArgs& a, hipStream_t st) {
   constexpr bool up = EPI == EP_UP;
